@@ -77,7 +77,10 @@ typedef struct {
                                wavefront, x neighbours exchanged by cross-lane moves
                                (1 <= h <= 3), one wavefront per work-group; 4 and 5 the same
                                kernel with two and four wavefronts (twice and four times the
-                               trials) per work-group.  Other values: HMC_EINVAL. */
+                               trials) per work-group.  0 and 3 take relaxations long enough for
+                               it (h = 2 and 3; nickel: from 149 and 232 steps) by conjugate
+                               gradients with the heavy-ball steps carried out in their Krylov
+                               basis: the same energies to rounding.  Other values: HMC_EINVAL. */
     int32_t zone_screen;    /* 1: skip the zone solve of a trial whose rejection is already
                                certain: the point-zone energy 1/2 sigma_p.(S_old - S_new) sigma_p
                                is a lower bound of the zone's (its relaxation only adds

@@ -91,7 +91,7 @@ hmc_replica replica_of_params(const hmc_params* p, int32_t Q)
 // workspace layout
 // ------------------------------------------------------------------------------------
 struct Layout {
-    size_t spins, Ctab, Stab, sigma, u0, u1, w, list, accept, state, partials, sums, seq_state, counters, stats,
+    size_t spins, Ctab, Stab, Ptab, sigma, u0, u1, w, list, accept, state, partials, sums, seq_state, counters, stats,
         thr, tex, hist, bonds, reps, pass_rep, node_rep, tile_rep, sweep, total;
     int64_t sites, grains, max_list;
     int pass_blocks, node_blocks, tile_blocks, tile_z, tile_y;
@@ -183,6 +183,7 @@ Layout layout_of(const hmc_params* p, int n, const hmc_replica* r)
     L.spins = take(S * sizeof(int16_t));
     L.Ctab = take((size_t)L.grains * kTab * sizeof(float));
     L.Stab = take((size_t)L.grains * kTab * sizeof(float));
+    L.Ptab = L.elastic ? take((size_t)L.grains * kProj * sizeof(float)) : 0;
     L.sigma = L.elastic ? take(6 * S * sizeof(float)) : 0;
     L.u0 = L.elastic ? take(3 * S * sizeof(float)) : 0;
     L.u1 = L.elastic ? take(3 * S * sizeof(float)) : 0;
@@ -269,6 +270,16 @@ void grain_tables(const double e[3], double C11, double C12, double C44, double 
             Cl[6 * I + J] = c;
             Sl[6 * I + J] = s;
         }
+}
+
+// Projectors a_i a_j on the first two crystal axes (kProj).
+void axis_projectors(const double e[3], float P[kProj])
+{
+    static const int pi[6] = {0, 1, 2, 1, 0, 0}, pj[6] = {0, 1, 2, 2, 2, 1};
+    double A[3][3];
+    bunge(e, A);
+    for (int m = 0; m < 2; ++m)
+        for (int I = 0; I < 6; ++I) P[6 * m + I] = (float)(A[pi[I]][m] * A[pj[I]][m]);
 }
 
 // Derivatives of the lab tables with respect to the three Euler angles (phi1, Phi, phi2):
@@ -556,6 +567,7 @@ hmc_status build_context(const hmc_params* p, int n, const hmc_replica* r, void*
     c->d.Ctab = (float*)(b + L.Ctab);
     c->d.Stab = (float*)(b + L.Stab);
     if (L.elastic) {
+        c->d.Ptab = (float*)(b + L.Ptab);
         c->d.sigma = (float*)(b + L.sigma);
         c->d.u[0] = (float*)(b + L.u0);
         c->d.u[1] = (float*)(b + L.u1);
@@ -680,7 +692,7 @@ hmc_status build_context(const hmc_params* p, int n, const hmc_replica* r, void*
 hmc_status upload_tables(hmc_ctx c, int rep, const double* euler)
 {
     const RepDev& R = c->reps[rep];
-    std::vector<float> Ct((size_t)R.Q * kTab, 0.f), St((size_t)R.Q * kTab, 0.f);
+    std::vector<float> Ct((size_t)R.Q * kTab, 0.f), St((size_t)R.Q * kTab, 0.f), Pt((size_t)R.Q * kProj);
     for (int64_t g = 0; g < R.Q; ++g) {
         for (int k = 0; k < 3; ++k)
             if (!std::isfinite(euler[3 * g + k])) return state_fail(c, HMC_ENUMERIC, "non-finite Euler angle");
@@ -691,7 +703,12 @@ hmc_status upload_tables(hmc_ctx c, int rep, const double* euler)
                 Ct[(size_t)g * kTab + sym_index(i, j)] = (float)Cl[6 * i + j];
                 St[(size_t)g * kTab + sym_index(i, j)] = (float)Sl[6 * i + j];
             }
+        axis_projectors(euler + 3 * g, &Pt[(size_t)g * kProj]);
     }
+    if (c->elastic_buffers)
+        HMC_TRY(c, hipMemcpyAsync(c->d.Ptab + R.grain_off * kProj, Pt.data(), Pt.size() * sizeof(float),
+                                  hipMemcpyHostToDevice, c->stream),
+                "orientations");
     HMC_TRY(c, hipMemcpyAsync(c->d.Ctab + R.grain_off * kTab, Ct.data(), Ct.size() * sizeof(float),
                               hipMemcpyHostToDevice, c->stream),
             "orientations");

@@ -19,6 +19,9 @@ namespace hmc {
 // Per-grain tables on the device: the 21 distinct entries of a symmetric 6x6 Voigt matrix,
 // upper triangle row by row, padded to 24 floats (96 bytes).
 constexpr int kTab = 24;
+// Projectors on two of a grain's crystal axes (a_i a_j in the Voigt order xx, yy, zz, yz, xz, xy
+// for the lab components a of the first and second axis): 12 floats.
+constexpr int kProj = 12;
 
 __host__ __device__ constexpr int sym_index(int i, int j)
 {
@@ -145,6 +148,7 @@ struct DeviceState {
     int16_t* spins = nullptr;        // sum of n3
     float* Ctab = nullptr;           // sum of Q, x kTab
     float* Stab = nullptr;
+    float* Ptab = nullptr;           // sum of Q, x kProj
     float* sigma = nullptr;          // 6 planes of total sites
     float* u[2] = {nullptr, nullptr};  // 3 planes each (ping-pong)
     float* w = nullptr;              // 3 planes

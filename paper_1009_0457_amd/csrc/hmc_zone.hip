@@ -25,12 +25,16 @@ hipError_t launch_zone_pass(hmc_ctx_s* c, int colour, hmc_trial_record* rec)
     a.beta = (float)c->p.zone_beta;
     const int h = c->p.zone_h;
     // automatic: lane shifts for h >= 1 (at h = 3, 1.67e6 solves/s against 3.75e5 for a
-    // wavefront per trial, 128^3 workload, n_r = 400); node columns for h = 0
+    // wavefront per trial, 128^3 workload, n_r = 400), for long relaxations at h = 2 and 3 with
+    // conjugate gradients; node columns for h = 0
     const int v = c->p.zone_variant;
+    const bool krylov = (v == 0 || v == 3) && krylov_pays(c->p);
     const bool laneshift = (v == 0 && h >= 1) || v == 3 || v == 4 || v == 5;
     const bool column = !laneshift && ((v == 0 && h <= 2) || v == 2);
     const int tok = prof_begin(c, kProfZone);
-    if (laneshift) {
+    if (krylov) {
+        launch_zone_krylov(c->p, c->max_list, c->d.Ptab, c->stream, a);
+    } else if (laneshift) {
         const int waves = v == 4 ? 2 : v == 5 ? 4 : 1;
         const int tw = h == 1 ? LaneShiftShape<1>::TW : h == 2 ? LaneShiftShape<2>::TW : LaneShiftShape<3>::TW;
         const int per_wg = tw * waves;

@@ -9,7 +9,8 @@
 // centre-point strain of voxel v from its 8 corners; C_v the stiffness of the pass's
 // snapshot spin at v, except C_new at the trial site.
 //
-// Three kernels compute this solve with different layouts (hmc_params.zone_variant):
+// Three kernels compute this solve step by step with different layouts (hmc_params.zone_variant; a
+// fourth, hmc_zone_krylov.hip, takes long relaxations by conjugate gradients):
 // k_zone (a wavefront per trial), k_zone_col (node columns of several trials across a
 // 256-lane work-group) and k_zone_lane (whole trials inside one wavefront, x neighbours by
 // cross-lane moves; the default for h = 1, 2, 3).  State and arithmetic are FP32; the final
@@ -895,5 +896,10 @@ __global__ __launch_bounds__(64 * WAVES, H == 1 ? 3 : 2) void k_zone_lane(ZoneAr
 // can give each its own scheduling options.
 hipError_t launch_zone_lane_h2(int waves, dim3 grid, dim3 block, hipStream_t stream, const ZoneArgs& a);
 hipError_t launch_zone_lane_h3(int waves, dim3 grid, dim3 block, hipStream_t stream, const ZoneArgs& a);
+
+// Whether conjugate gradients (hmc_zone_krylov.hip) serve these parameters' zone solve and are
+// faster than its heavy-ball steps, and the launch over at most max_list trials.
+bool krylov_pays(const hmc_params& p);
+void launch_zone_krylov(const hmc_params& p, int64_t max_list, const float* Ptab, hipStream_t stream, ZoneArgs a);
 
 }  // namespace hmc
