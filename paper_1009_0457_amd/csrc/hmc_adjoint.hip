@@ -206,7 +206,7 @@ struct AdjStepArgs {
 };
 
 // tau = C_q eta and, where `owned`, gq_k = eta . (dC_{q,k} eps) for the three angles k,
-// with the tables of a wavefront's first two grains from scalar loads (as symv21_grains);
+// with the tables of a wavefront's first two grains from scalar loads;
 // wavefronts with more grains gather per lane.
 __device__ __forceinline__ void adjoint_voxel(const float* Ctab, const float* dC, int q, bool owned,
                                               const float eta[6], const float eps[6], float tau[6], double gq[3])

@@ -272,14 +272,15 @@ void grain_tables(const double e[3], double C11, double C12, double C44, double 
         }
 }
 
-// Projectors a_i a_j on the first two crystal axes (kProj).
-void axis_projectors(const double e[3], float P[kProj])
+// The projectors on the first two crystal axes, times sqrt(|C11 - C12 - 2 C44| / C44) (kProj).
+void axis_projectors(const double e[3], double C11, double C12, double C44, float P[kProjUsed])
 {
+    const double sa = std::sqrt(std::fabs(C11 - C12 - 2.0 * C44) / C44);
     static const int pi[6] = {0, 1, 2, 1, 0, 0}, pj[6] = {0, 1, 2, 2, 2, 1};
     double A[3][3];
     bunge(e, A);
     for (int m = 0; m < 2; ++m)
-        for (int I = 0; I < 6; ++I) P[6 * m + I] = (float)(A[pi[I]][m] * A[pj[I]][m]);
+        for (int I = 0; I < 6; ++I) P[6 * m + I] = (float)(sa * A[pi[I]][m] * A[pj[I]][m]);
 }
 
 // Derivatives of the lab tables with respect to the three Euler angles (phi1, Phi, phi2):
@@ -692,7 +693,7 @@ hmc_status build_context(const hmc_params* p, int n, const hmc_replica* r, void*
 hmc_status upload_tables(hmc_ctx c, int rep, const double* euler)
 {
     const RepDev& R = c->reps[rep];
-    std::vector<float> Ct((size_t)R.Q * kTab, 0.f), St((size_t)R.Q * kTab, 0.f), Pt((size_t)R.Q * kProj);
+    std::vector<float> Ct((size_t)R.Q * kTab, 0.f), St((size_t)R.Q * kTab, 0.f), Pt((size_t)R.Q * kProj, 0.f);
     for (int64_t g = 0; g < R.Q; ++g) {
         for (int k = 0; k < 3; ++k)
             if (!std::isfinite(euler[3 * g + k])) return state_fail(c, HMC_ENUMERIC, "non-finite Euler angle");
@@ -703,7 +704,7 @@ hmc_status upload_tables(hmc_ctx c, int rep, const double* euler)
                 Ct[(size_t)g * kTab + sym_index(i, j)] = (float)Cl[6 * i + j];
                 St[(size_t)g * kTab + sym_index(i, j)] = (float)Sl[6 * i + j];
             }
-        axis_projectors(euler + 3 * g, &Pt[(size_t)g * kProj]);
+        axis_projectors(euler + 3 * g, c->p.C11, c->p.C12, c->p.C44, &Pt[(size_t)g * kProj]);
     }
     if (c->elastic_buffers)
         HMC_TRY(c, hipMemcpyAsync(c->d.Ptab + R.grain_off * kProj, Pt.data(), Pt.size() * sizeof(float),

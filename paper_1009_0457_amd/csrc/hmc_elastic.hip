@@ -13,13 +13,15 @@
 // fixed-point accumulators; the next step's blocks first advance E from them, and
 // k_seq_fold does so after a sequence's last step.  k_global_final writes the stress field
 // the zone solves read.
+#include <cmath>
+
 #include "hmc_device.h"
 
 namespace hmc {
 
 struct GlobArgs {
     const int16_t* spins;
-    const float* Ctab;
+    CubicTab C;
     const float* uin;
     float* uout;
     float* w;
@@ -109,7 +111,8 @@ __global__ __launch_bounds__(32 * TY, TY == 8 ? 4 : TY == 16 ? 2 : 1) void k_glo
     const int x0 = bx * kTileX, y0 = by * TY, z0 = bz * tz;
     const int z1 = (z0 + tz < K) ? z0 + tz : K;
     const int16_t* spins = a.spins + R.site_off;
-    const float* Ctab = a.Ctab + R.grain_off * kTab;
+    CubicTab C = a.C;
+    C.P += R.grain_off * kProj;
     const float* uin = a.uin + R.site_off;
     float* uout = a.uout + R.site_off;
     float* w = a.w + R.site_off;
@@ -129,7 +132,7 @@ __global__ __launch_bounds__(32 * TY, TY == 8 ? 4 : TY == 16 ? 2 : 1) void k_glo
     }
     if (lb == R.tile_first && threadIdx.x < kSumSlots) a.sums_clear[(int64_t)r * kSumSlots + threadIdx.x] = 0ull;
     float E[6];
-    const float alpha4 = 0.25f * R.glob_alpha, beta = R.glob_beta;
+    const float alpha4 = 0.25f * R.glob_alpha * C.C44, beta = R.glob_beta;
     const int t = threadIdx.x, lx = t % kTileX, ly = t / kTileX;
     const int nx = x0 + lx, ny = y0 + ly;
     const bool own = nx < K && ny < K;
@@ -190,13 +193,14 @@ __global__ __launch_bounds__(32 * TY, TY == 8 ? 4 : TY == 16 ? 2 : 1) void k_glo
             }
         }
     };
-    // stress of voxel position k of the layer whose node pair is in sNa / sNb (grains in q)
+    // stress (in units of C44) of voxel position k of the layer whose node pair is in sNa / sNb
+    // (grains in q)
     auto voxel_stress = [&](int k, int q, float s6[6]) {
         int ix, iy;
         step_voxel_pos<TY>(t + THREADS * k, ix, iy);
         float e[6];
         pair_strain<NX>(sNa, sNb, ix, iy, E, e);
-        symv21_grains(Ctab, q, e, s6);
+        cubic_grains<NT>(C, q, e, s6);
     };
 
     // prologue: node layers z0-1, z0 -> voxel layer z0-1 (kept in registers)
@@ -285,7 +289,8 @@ __global__ __launch_bounds__(32 * TY, TY == 8 ? 4 : TY == 16 ? 2 : 1) void k_glo
     const int k = threadIdx.x & 255;             // total k of the half threadIdx.x / 256
     if (k < 6) {
         const unsigned copy = (unsigned)(lb - R.tile_first + (threadIdx.x >> 8)) & (kSumCopies - 1);
-        atomicAdd(a.sums_out + (int64_t)r * kSumSlots + copy * 8 + k, (unsigned long long)llrint(tot * kSumScale));
+        atomicAdd(a.sums_out + (int64_t)r * kSumSlots + copy * 8 + k,
+                  (unsigned long long)llrint(tot * (kSumScale * (double)C.C44)));
     }
 }
 
@@ -303,7 +308,8 @@ __global__ void k_seq_fold(double* state, const double* st_last, const unsigned 
 
 struct FinalArgs {
     const int16_t* spins;
-    const float* Ctab;
+    const float* P;         // CubicTab's rows, and its constants in double
+    double lam, sa, sgn, C44;
     const float* u;
     float* sigma;       // may be null
     double* partials;
@@ -313,31 +319,38 @@ struct FinalArgs {
     int64_t plane;
 };
 
+// The strain's sum and the stress are formed in double (once per refresh, and memory bound): what is
+// left of the error is the displacements' and the table's.
 __global__ __launch_bounds__(256) void k_global_final(FinalArgs a)
 {
     const NodeRange nr = node_range(a.reps, a.node_rep);
     const RepDev& R = nr.R;
     const int K = R.K;
     const double* st = a.state + (int64_t)a.node_rep[blockIdx.x] * kStateDoubles;
-    float E[6];
-#pragma unroll
-    for (int I = 0; I < 6; ++I) E[I] = (float)st[kE + I];
     const int16_t* spins = a.spins + R.site_off;
-    const float* Ctab = a.Ctab + R.grain_off * kTab;
+    const float* Ptab = a.P + R.grain_off * kProj;
     const float* u = a.u + R.site_off;
+    const float zero[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     double U[1] = {0.0};
     for (int64_t v = nr.first; v < R.n3; v += nr.stride) {
         const int x = (int)(v % K), y = (int)((v / K) % K), z = (int)(v / ((int64_t)K * K));
-        float e[6], s[6];
-        voxel_strain(u, a.plane, K, x, y, z, E, e);
-        symv21(Ctab + (int64_t)spins[v] * kTab, e, s);
+        float g[6], c[kProjUsed];
+        voxel_strain(u, a.plane, K, x, y, z, zero, g);
+        cubic_row(Ptab, spins[v], c);
+        double e[6], s[6];
+#pragma unroll
+        for (int I = 0; I < 6; ++I) e[I] = st[kE + I] + (double)g[I];
+        cubic_stress(c, a.lam, a.sa, a.sgn, 1.0, e, s);
         double d = 0.0;
 #pragma unroll
-        for (int I = 0; I < 6; ++I) d += (double)s[I] * (double)e[I];
+        for (int I = 0; I < 6; ++I) {
+            s[I] *= a.C44;
+            d += s[I] * e[I];
+        }
         U[0] += 0.5 * d;
         if (a.sigma)
 #pragma unroll
-            for (int I = 0; I < 6; ++I) a.sigma[(int64_t)I * a.plane + R.site_off + v] = s[I];
+            for (int I = 0; I < 6; ++I) a.sigma[(int64_t)I * a.plane + R.site_off + v] = (float)s[I];
     }
     block_sum_to<1>(a.partials, U);
 }
@@ -456,6 +469,13 @@ __global__ __launch_bounds__(256) void k_texture(const int16_t* spins, const int
 
 // ---- launchers ----
 
+static CubicTab cubic_tab(const hmc_ctx_s* c)
+{
+    const double an = (c->p.C11 - c->p.C12 - 2.0 * c->p.C44) / c->p.C44;
+    return {c->d.Ptab, (float)(c->p.C12 / c->p.C44), (float)std::sqrt(std::fabs(an)), an < 0 ? -1.f : 1.f,
+            (float)c->p.C44};
+}
+
 hipError_t launch_reuss(hmc_ctx_s* c)
 {
     ReussArgs a;
@@ -484,7 +504,7 @@ hipError_t seq_step(hmc_ctx_s* c, hipStream_t s, int i, const float* uin, float*
     const int64_t per = (int64_t)c->n_rep * kSumSlots;
     GlobArgs a;
     a.spins = c->d.spins;
-    a.Ctab = c->d.Ctab;
+    a.C = cubic_tab(c);
     a.uin = uin;
     a.uout = uout;
     a.w = c->d.w;
@@ -549,7 +569,12 @@ hipError_t launch_global_final(hmc_ctx_s* c, bool write_sigma)
 {
     FinalArgs a;
     a.spins = c->d.spins;
-    a.Ctab = c->d.Ctab;
+    const double an = (c->p.C11 - c->p.C12 - 2.0 * c->p.C44) / c->p.C44;
+    a.P = c->d.Ptab;
+    a.lam = c->p.C12 / c->p.C44;
+    a.sa = std::sqrt(std::fabs(an));
+    a.sgn = an < 0 ? -1.0 : 1.0;
+    a.C44 = c->p.C44;
     a.u = c->d.u[c->cur_u];
     a.sigma = write_sigma ? c->d.sigma : nullptr;
     a.partials = c->d.partials;

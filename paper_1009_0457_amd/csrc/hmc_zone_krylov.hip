@@ -26,12 +26,11 @@
 // so that the dot products are sums over whole DPP rows.  Lanes past a trial's own have zero
 // stiffness and vectors that stay zero; they share the trial's LDS block, where they only ever write
 // the zeros already there.  The stiffness of a voxel is held as the projectors P1, P2 on two of its
-// crystal axes (12 registers in place of 21, for the vectors' sake): for cubic crystals
-// C e = C12 tr(e) 1 + 2 C44 e + (C11 - C12 - 2 C44) sum_a (P_a : e) P_a, and the three projectors add
-// up to 1.
+// crystal axes (12 registers in place of 21, for the vectors' sake).
 #include <algorithm>
 #include <cmath>
 
+#include "hmc_device.h"
 #include "hmc_zone_kernels.h"
 
 namespace hmc {
@@ -80,23 +79,6 @@ __device__ __forceinline__ float group_sum(float v)
     return v;
 }
 
-// C e / C44 of a cubic crystal from the projectors on two of its axes (P1 in c[0..5], P2 in
-// c[6..11]): lam = C12 / C44, an = (C11 - C12 - 2 C44) / C44 and on = 1; zero with all three 0.
-__device__ __forceinline__ void cubic_stress(const float c[12], float lam, float an, float on, const float e[6],
-                                             float s[6])
-{
-    const float tr = e[0] + e[1] + e[2];
-    const float p1 = c[0] * e[0] + c[1] * e[1] + c[2] * e[2] + c[3] * e[3] + c[4] * e[4] + c[5] * e[5];
-    const float p2 = c[6] * e[0] + c[7] * e[1] + c[8] * e[2] + c[9] * e[3] + c[10] * e[4] + c[11] * e[5];
-    const float p3 = (tr - p1) - p2;
-    const float h = lam * tr + an * p3;
-    const float q1 = an * (p1 - p3), q2 = an * (p2 - p3);
-#pragma unroll
-    for (int I = 0; I < 3; ++I) s[I] = ((on + on) * e[I] + h) + q1 * c[I] + q2 * c[6 + I];
-#pragma unroll
-    for (int I = 3; I < 6; ++I) s[I] = on * e[I] + q1 * c[I] + q2 * c[6 + I];
-}
-
 // Corner forces of one node layer, as node_forces: the own node's and the +y node's.
 __device__ __forceinline__ void corner_forces(float L0, float L1, float L2, float& own, float& ny)
 {
@@ -109,7 +91,7 @@ __device__ __forceinline__ void corner_forces(float L0, float L1, float L2, floa
 struct KrylovArgs {
     ZoneArgs z;
     const float* Ptab;      // per-grain projectors (kProj)
-    float lam, an;          // C12 / C44 and (C11 - C12 - 2 C44) / C44
+    float lam, sa, sgn;     // CubicTab's constants
     float inv_scale;        // C44 / 16: the kernel's operator is 16 / C44 times A
 };
 
@@ -134,7 +116,7 @@ __global__ __launch_bounds__(64, 2) void k_zone_krylov(KrylovArgs ka)
     const bool vox = member && x < N;
     const bool centre_col = vox && x == H && y == H;
     const uint32_t count = *a.count;
-    const float on_vox = vox ? 1.f : 0.f, lam = vox ? ka.lam : 0.f, an = vox ? ka.an : 0.f;
+    const float on_vox = vox ? 1.f : 0.f, lam = vox ? ka.lam : 0.f, sa = vox ? ka.sa : 0.f;
 
     float* const ub = s_u + zs * TB;                              // this lane's trial block
     float* const nbk = s_n + S::PAD + zs * TB;
@@ -190,11 +172,11 @@ __global__ __launch_bounds__(64, 2) void k_zone_krylov(KrylovArgs ka)
         const uint32_t e = base + (uint32_t)zs;
         const bool active = member && e < count;
 
-        float Cv[N][12];
+        float Cv[N][kProjUsed];
 #pragma unroll
         for (int k = 0; k < N; ++k)
 #pragma unroll
-            for (int i = 0; i < 12; ++i) Cv[k][i] = 0.f;
+            for (int i = 0; i < kProjUsed; ++i) Cv[k][i] = 0.f;
         if (l == 0) {
             s_nb2[zs] = 0.0;
 #pragma unroll
@@ -243,15 +225,7 @@ __global__ __launch_bounds__(64, 2) void k_zone_krylov(KrylovArgs ka)
                 for (int k = 0; k < N; ++k) {
                     const int gz = ((pz + k - H) % K + K) % K;
                     const int g = (centre_col && k == H) ? q_new : (int)tc.spins[gx + K * (gy + K * gz)];
-                    const float4* t = reinterpret_cast<const float4*>(Ptab + (int64_t)g * kProj);
-#pragma unroll
-                    for (int i = 0; i < 3; ++i) {
-                        const float4 v = t[i];
-                        Cv[k][4 * i] = v.x;
-                        Cv[k][4 * i + 1] = v.y;
-                        Cv[k][4 * i + 2] = v.z;
-                        Cv[k][4 * i + 3] = v.w;
-                    }
+                    cubic_row(Ptab, g, Cv[k]);
                 }
             }
         }
@@ -300,7 +274,7 @@ __global__ __launch_bounds__(64, 2) void k_zone_krylov(KrylovArgs ka)
                 float Pp[3], Qp[3], Rp[3];
                 strains(p, [&](int kz, const float (&ev)[6]) {
                     float sv[6];
-                    cubic_stress(Cv[kz], lam, an, on_vox, ev, sv);
+                    cubic_stress<float>(Cv[kz], lam, sa, ka.sgn, on_vox, ev, sv);
                     const float Pn[3] = {sv[0], sv[5], sv[4]};
                     const float Qn[3] = {sv[5], sv[1], sv[3]};
                     const float Rn[3] = {sv[4], sv[3], sv[2]};
@@ -406,7 +380,7 @@ __global__ __launch_bounds__(64, 2) void k_zone_krylov(KrylovArgs ka)
             double quad = 0.0, lin = 0.0;
             strains(u, [&](int kz, const float (&ev)[6]) {
                 float sv[6];
-                cubic_stress(Cv[kz], lam, an, on_vox, ev, sv);
+                cubic_stress<float>(Cv[kz], lam, sa, ka.sgn, on_vox, ev, sv);
 #pragma unroll
                 for (int I = 0; I < 6; ++I) quad += (double)ev[I] * (double)sv[I];
                 if (kz == H && centre_col) {
@@ -528,7 +502,9 @@ void launch_zone_krylov(const hmc_params& p, int64_t max_list, const float* Ptab
     a.z = za;
     a.Ptab = Ptab;
     a.lam = (float)(p.C12 / p.C44);
-    a.an = (float)((p.C11 - p.C12 - 2.0 * p.C44) / p.C44);
+    const double an = (p.C11 - p.C12 - 2.0 * p.C44) / p.C44;
+    a.sa = (float)std::sqrt(std::fabs(an));
+    a.sgn = an < 0 ? -1.f : 1.f;
     a.inv_scale = (float)(p.C44 / 16.0);
     const int tw = p.zone_h == 2 ? KrylovShape<2>::TW : KrylovShape<3>::TW;
     // many more work-groups than resident slots: the hardware's dispatch balances the tail
