@@ -117,6 +117,7 @@ int balanced_depth(int t, int K)
 // 2: 15.1 us per step on 256 blocks of 16 rows against 14.6 us on 512 of 8).
 int tile_rows_of(int n, const hmc_replica* r, int tz)
 {
+    if (tz <= kFlatDepth) return 8;
     for (int ty = 32; ty >= 16; ty /= 2) {
         int64_t blocks = 0;
         bool fits = true;
@@ -138,21 +139,29 @@ int tile_rows_of(int n, const hmc_replica* r, int tz)
 // 1.73 against 1.66 ms.
 bool step_streams_of(int64_t sites) { return sites * 38 > (int64_t)512 << 20; }
 
-// Node layers per block of the tiled explicit step: the caller's choice, else the deepest
-// tile that still launches at least 1024 blocks of 32 x 8 nodes over all replicas (4 per
-// compute unit), but 2 rather than 1 (a block's first layer is redone by
-// its neighbour, which one-layer tiles pay on every layer), and 1 when no depth reaches it.
-// Measured with 32 x 8 tiles: 32 at 256^3 and 512^3 (64 is within 1 %), 8 at 128^3, 2 at 64^3
-// are the fastest depths there.
+// Node layers per block of the explicit step: the caller's choice, else by the number of 32 x 8 blocks
+// the replicas give at each depth.  Deep tiles (8 and more, marched layer by layer) redo the least halo
+// work but want the chip full; below that the step is a chain of memory latencies, and the shallow
+// kernel (k_global_step_flat) takes the depth at which its blocks are all resident, two per compute unit.
+// Measured single lattices, us per step at depth 1 / 2 / 4 / 8 / 16:
+//   32^3 5.3 / 6.1 / 8.0 / 17 / -      48^3 9.3 / 7.8 / 8.4 / 18 / -     64^3 10.6 / 8.4 / 9.0 / 18 / 29
+//   72^3 19 / 16.1 / 14.8 / 18.7 / 29  80^3 22 / 17.7 / 19.8 / 20.9 / 31  96^3 34 / 26 / 27 / 21.4 / 31
+//   100^3 44 / 36 / 38 / 24.4 / 34     128^3 64 / 53 / 52 / 27.3 / 36     144^3 - / 82 / 80 / 48.4 / 45.6
+//   160^3 - / 100 / 99 / 50.5 / 47.4   192^3 - / 182 / 177 / 113 / 99
+// and 32 at 256^3 and 512^3 (64 is within 1 %).
 int tile_depth_of(const hmc_params* p, int n, const hmc_replica* r)
 {
     if (p->refresh_tile_z > 0) return p->refresh_tile_z;
-    for (int tz = kTileZMax; tz >= 1; tz /= 2) {
-        int64_t blocks = 0;
-        for (int i = 0; i < n; ++i) blocks += tile_blocks_of(r[i].K, tz, 8);
-        if (blocks >= 1024) return tz > 1 ? tz : 2;
-    }
-    return 1;
+    auto blocks = [&](int tz) {
+        int64_t b = 0;
+        for (int i = 0; i < n; ++i) b += tile_blocks_of(r[i].K, tz, 8);
+        return b;
+    };
+    if (blocks(32) >= 1024) return 32;
+    if (blocks(16) >= 800) return 16;
+    if (blocks(8) >= 400) return 8;
+    if (blocks(1) <= 256) return 1;
+    return blocks(2) > 512 && blocks(4) <= 512 ? 4 : 2;
 }
 
 Layout layout_of(const hmc_params* p, int n, const hmc_replica* r)
@@ -562,6 +571,9 @@ hmc_status build_context(const hmc_params* p, int n, const hmc_replica* r, void*
     c->node_blocks = L.node_blocks;
     c->tile_blocks = L.tile_blocks;
     c->step_streams = step_streams_of(L.sites);
+    c->flat_depth = L.tile_y == 8 && L.tile_z <= kFlatDepth && !c->step_streams ? L.tile_z : 0;
+    for (int i = 0; i < n; ++i)
+        if (balanced_depth(L.tile_z, r[i].K) != c->flat_depth) c->flat_depth = 0;
     c->elastic_buffers = L.elastic;
     char* b = (char*)ws;
     c->d.spins = (int16_t*)(b + L.spins);

@@ -247,6 +247,34 @@ __device__ __forceinline__ void voxel_strain(const float* __restrict__ u, int64_
     e[5] = E[5] + g[0][1] + g[1][0];
 }
 
+// Sum over a wavefront in every lane: the butterfly over lanes 32, 16, 8, 4, 2 and 1 apart, by register
+// exchanges of halves and rows and DPP moves (both lanes of a pair form the same sum; the moves by 8 and
+// 4 rotate a row, which after the sums above is periodic in 16 and 8 lanes).
+template <class F>
+__device__ __forceinline__ double lanes_moved(double v, F&& move)
+{
+    return __hiloint2double(move(__double2hiint(v)), move(__double2loint(v)));
+}
+
+__device__ __forceinline__ double wave_sum(double v)
+{
+    {
+        const auto h = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(v), (unsigned)__double2hiint(v), false, false);
+        const auto l = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(v), (unsigned)__double2loint(v), false, false);
+        v = __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+    }
+    {
+        const auto h = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(v), (unsigned)__double2hiint(v), false, false);
+        const auto l = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(v), (unsigned)__double2loint(v), false, false);
+        v = __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+    }
+    v += lanes_moved(v, [](int w) { return __builtin_amdgcn_update_dpp(0, w, 0x128, 0xf, 0xf, true); });   // row_ror:8
+    v += lanes_moved(v, [](int w) { return __builtin_amdgcn_update_dpp(0, w, 0x124, 0xf, 0xf, true); });   // row_ror:4
+    v += lanes_moved(v, [](int w) { return __builtin_amdgcn_update_dpp(0, w, 0x4E, 0xf, 0xf, true); });    // quad_perm [2, 3, 0, 1]
+    v += lanes_moved(v, [](int w) { return __builtin_amdgcn_update_dpp(0, w, 0xB1, 0xf, 0xf, true); });    // quad_perm [1, 0, 3, 2]
+    return v;
+}
+
 // Sum over the 256 threads of a block of v[k], k < NVALS, in a fixed order: a butterfly
 // within each wavefront (both lanes of a pair form the same sum), then the four wavefront
 // sums in order.  Thread k < NVALS receives total k; the other threads receive 0.
@@ -256,11 +284,7 @@ __device__ __forceinline__ double block_total(const double v[NVALS])
     __shared__ double red[NVALS][4];
     double s[NVALS];
 #pragma unroll
-    for (int k = 0; k < NVALS; ++k) s[k] = v[k];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-        for (int k = 0; k < NVALS; ++k) s[k] += __shfl_xor(s[k], o, 64);
+    for (int k = 0; k < NVALS; ++k) s[k] = wave_sum(v[k]);
     const int t = threadIdx.x;
     if ((t & 63) == 0)
 #pragma unroll
@@ -278,11 +302,7 @@ __device__ __forceinline__ double block_total_quads(const double v[NVALS])
     __shared__ double red[NVALS][4 * Q];
     double s[NVALS];
 #pragma unroll
-    for (int k = 0; k < NVALS; ++k) s[k] = v[k];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-        for (int k = 0; k < NVALS; ++k) s[k] += __shfl_xor(s[k], o, 64);
+    for (int k = 0; k < NVALS; ++k) s[k] = wave_sum(v[k]);
     const int t = threadIdx.x;
     if ((t & 63) == 0)
 #pragma unroll

@@ -36,15 +36,32 @@ struct GlobArgs {
     const int32_t* tile_rep;
     int64_t plane;
     int order;                           // logical block order (hmc_set_block_order)
+    int single;                          // one replica, described here: no table to read first
+    int K, tile_z;
+    float alpha, beta;
 };
+
+// What a step's block needs of its replica at once.
+struct StepRep {
+    int r, K, tile_z, tile_first;
+    float alpha, beta;
+    int64_t site_off, grain_off;
+};
+
+__device__ __forceinline__ StepRep step_rep(const GlobArgs& a, int lb)
+{
+    if (a.single) return {0, a.K, a.tile_z, 0, a.alpha, a.beta, 0, 0};
+    const int r = a.tile_rep[lb];
+    const RepDev& R = a.reps[r];
+    return {r, R.K, R.tile_z, R.tile_first, R.glob_alpha, R.glob_beta, R.site_off, R.grain_off};
+}
 
 // (E, wE) of the step after the one that started from st_in and whose stress sums are in
 // sums (Sec. 5's average-stress control: r_E = Sigma - <sigma>, wE <- beta wE + alphaE r_E,
 // E <- E + wE), component I; sums == null: st_in unchanged.
-__device__ __forceinline__ void advance_E(const RepDev* reps, int r, const double* st_in, int stride,
+__device__ __forceinline__ void advance_E(const RepDev& R, int r, const double* st_in, int stride,
                                           const unsigned long long* sums, int I, double& E_I, double& wE_I)
 {
-    const RepDev& R = reps[r];
     E_I = st_in[(int64_t)r * stride + I];
     wE_I = st_in[(int64_t)r * stride + 6 + I];
     if (sums) {
@@ -100,9 +117,8 @@ __global__ __launch_bounds__(32 * TY, TY == 8 ? 4 : TY == 16 ? 2 : 1) void k_glo
     __shared__ float4 sraw[3][TY][kTileX];
 
     const int lb = logical_block((int)blockIdx.x, (int)gridDim.x, a.order);   // neighbouring tiles share an L2
-    const int r = a.tile_rep[lb];
-    const RepDev R = a.reps[r];
-    const int K = R.K;
+    const StepRep R = step_rep(a, lb);
+    const int r = R.r, K = R.K;
     const int ntx = (K + kTileX - 1) / kTileX, nty = (K + TY - 1) / TY, tz = R.tile_z;
     int b = lb - R.tile_first;
     const int bx = b % ntx;
@@ -122,7 +138,7 @@ __global__ __launch_bounds__(32 * TY, TY == 8 ? 4 : TY == 16 ? 2 : 1) void k_glo
     __shared__ double sE[6];
     if (threadIdx.x < 6) {
         double E_I, wE_I;
-        advance_E(a.reps, r, a.st_in, a.st_in_stride, a.sums_in, threadIdx.x, E_I, wE_I);
+        advance_E(a.reps[r], r, a.st_in, a.st_in_stride, a.sums_in, threadIdx.x, E_I, wE_I);
         sE[threadIdx.x] = E_I;
         if (lb == R.tile_first) {
             a.st_out[(int64_t)r * kSeqState + threadIdx.x] = E_I;
@@ -132,7 +148,7 @@ __global__ __launch_bounds__(32 * TY, TY == 8 ? 4 : TY == 16 ? 2 : 1) void k_glo
     }
     if (lb == R.tile_first && threadIdx.x < kSumSlots) a.sums_clear[(int64_t)r * kSumSlots + threadIdx.x] = 0ull;
     float E[6];
-    const float alpha4 = 0.25f * R.glob_alpha * C.C44, beta = R.glob_beta;
+    const float alpha4 = 0.25f * R.alpha * C.C44, beta = R.beta;
     const int t = threadIdx.x, lx = t % kTileX, ly = t / kTileX;
     const int nx = x0 + lx, ny = y0 + ly;
     const bool own = nx < K && ny < K;
@@ -273,7 +289,7 @@ __global__ __launch_bounds__(32 * TY, TY == 8 ? 4 : TY == 16 ? 2 : 1) void k_glo
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
                 const int64_t idx = (int64_t)j * P + n;
-                const float wn = beta * wz[j] - alpha4 * F[j];
+                const float wn = __builtin_fmaf(-alpha4, F[j], beta * wz[j]);
                 if (NT) {
                     __builtin_nontemporal_store(wn, &w[idx]);
                     __builtin_nontemporal_store(uz[j] + wn, &uout[idx]);
@@ -294,6 +310,142 @@ __global__ __launch_bounds__(32 * TY, TY == 8 ? 4 : TY == 16 ? 2 : 1) void k_glo
     }
 }
 
+// The step for shallow tiles (depth TZ = 1, 2 or 4: lattices whose blocks hardly fill the chip).  There the
+// march above is a chain of memory latencies, a layer's loads after another's; here a block of six
+// wavefronts issues every load of its 32 x 8 x TZ nodes at once (a thread a node column, a voxel column
+// and an own-node column), so the chain is arguments, fields and spins, the spins' stiffness rows, stores.
+// Voxels, sums and their order are those of the tiled step: the same bits.
+// Measured per step (kernel trace): 16^3 at depth 1 8.4 us tiled, 5.6 so; 64^3 at depth 2 12.0 and 8.4.
+constexpr int kFlatThreads = 384;
+template <int TZ>
+__global__ __launch_bounds__(kFlatThreads, 3) void k_global_step_flat(GlobArgs a)
+{
+    constexpr int NX = kTileX + 2, NY = kTileY + 2, VX = kTileX + 1, VY = kTileY + 1;
+    static_assert(NX * NY <= kFlatThreads && kStepVox <= kFlatThreads, "a thread a column");
+    __shared__ float4 sNa[TZ + 1][NY][NX];
+    __shared__ float2 sNb[TZ + 1][NY][NX];
+    __shared__ float4 sPa[TZ][VY][VX], sPb[TZ][VY][VX];
+    __shared__ double sE[6], red[6][4];
+
+    const int lb = logical_block((int)blockIdx.x, (int)gridDim.x, a.order);
+    const StepRep R = step_rep(a, lb);
+    const int r = R.r, K = R.K;
+    const int ntx = (K + kTileX - 1) / kTileX, nty = (K + kTileY - 1) / kTileY;
+    int b = lb - R.tile_first;
+    const int bx = b % ntx;
+    b /= ntx;
+    const int by = b % nty, bz = b / nty;
+    const int x0 = bx * kTileX, y0 = by * kTileY, z0 = bz * TZ;
+    const int16_t* spins = a.spins + R.site_off;
+    const float* uin = a.uin + R.site_off;
+    float* uout = a.uout + R.site_off;
+    float* w = a.w + R.site_off;
+    const int64_t P = a.plane;
+    const int t = threadIdx.x;
+    const int KK = K * K;
+
+    // spins first: the stiffness rows wait for them
+    int vx, vy;
+    step_voxel_pos(t, vx, vy);
+    const bool vox = t < kStepVox;
+    const int vox_xy = wrap_tile(x0 - 1 + vx, K) + K * wrap_tile(y0 - 1 + vy, K);
+    int sp[TZ + 1];
+#pragma unroll
+    for (int l = 0; l <= TZ; ++l) sp[l] = vox ? spins[vox_xy + (int64_t)KK * wrap_tile(z0 - 1 + l, K)] : 0;
+    const int ix = t % NX, iy = t / NX;
+    const bool node = t < NX * NY;
+    const int node_xy = wrap_tile(x0 - 1 + ix, K) + K * wrap_tile(y0 - 1 + iy, K);
+    float un[TZ + 2][3];
+#pragma unroll
+    for (int l = 0; l < TZ + 2; ++l) {
+        const int64_t n = node_xy + (int64_t)KK * wrap_tile(z0 - 1 + l, K);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) un[l][j] = node ? uin[j * P + n] : 0.f;
+    }
+    const int lx = t % kTileX, ly = t / kTileX;
+    const int64_t own_n = x0 + lx + (int64_t)K * (y0 + ly) + (int64_t)KK * z0;
+    const bool own = t < kTileX * kTileY && x0 + lx < K && y0 + ly < K;
+    float wz[TZ][3], uz[TZ][3];
+#pragma unroll
+    for (int l = 0; l < TZ; ++l)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const bool in = own && (TZ <= 2 || z0 + l < K);
+            wz[l][j] = in ? w[j * P + own_n + (int64_t)KK * l] : 0.f;
+            uz[l][j] = in ? uin[j * P + own_n + (int64_t)KK * l] : 0.f;
+        }
+    if (t >= kFlatThreads - 64 && t < kFlatThreads - 64 + 6) {   // the last wavefront has no voxels
+        const int I = t - (kFlatThreads - 64);
+        double E_I, wE_I;
+        advance_E(a.reps[r], r, a.st_in, a.st_in_stride, a.sums_in, I, E_I, wE_I);
+        sE[I] = E_I;
+        if (lb == R.tile_first) {
+            a.st_out[(int64_t)r * kSeqState + I] = E_I;
+            a.st_out[(int64_t)r * kSeqState + 6 + I] = wE_I;
+            if (a.E_record) a.E_record[I] = E_I;
+        }
+    }
+    if (lb == R.tile_first && t < kSumSlots) a.sums_clear[(int64_t)r * kSumSlots + t] = 0ull;
+    const float* rows = a.C.P + R.grain_off * kProj;
+    float c[TZ + 1][kProjUsed];
+#pragma unroll
+    for (int l = 0; l <= TZ; ++l) cubic_row(rows, sp[l], c[l]);
+    if (node) {
+#pragma unroll
+        for (int l = 0; l <= TZ; ++l) pair_node_entry(un[l + 1], un[l], sNa[l][iy][ix], sNb[l][iy][ix]);
+    }
+    __syncthreads();
+    double acc[6] = {0, 0, 0, 0, 0, 0};
+    if (vox) {
+        float E[6], s[2][6];
+#pragma unroll
+        for (int I = 0; I < 6; ++I) E[I] = (float)sE[I];
+#pragma unroll
+        for (int l = 0; l <= TZ; ++l) {
+            float e[6];
+            pair_strain<NX>(sNa[l], sNb[l], vx, vy, E, e);
+            cubic_stress(c[l], a.C, e, s[l & 1]);
+            if (l > 0) {
+                pair_voxel_entry(s[l & 1], s[(l & 1) ^ 1], sPa[l - 1][vy][vx], sPb[l - 1][vy][vx]);
+                if (vx >= 1 && vy >= 1 && x0 - 1 + vx < K && y0 - 1 + vy < K && (TZ <= 2 || z0 + l - 1 < K)) {
+#pragma unroll
+                    for (int I = 0; I < 6; ++I) acc[I] += (double)s[l & 1][I];
+                }
+            }
+        }
+    }
+    if (t < kTileX * kTileY) {   // whole wavefronts; the halo's voxels (the others) are not owned
+#pragma unroll
+        for (int I = 0; I < 6; ++I) {
+            const double v = wave_sum(acc[I]);
+            if ((t & 63) == 0) red[I][t >> 6] = v;
+        }
+    }
+    __syncthreads();
+    if (t < 6) {
+        const double tot = (red[t][0] + red[t][1]) + (red[t][2] + red[t][3]);
+        const unsigned copy = (unsigned)(lb - R.tile_first) & (kSumCopies - 1);
+        atomicAdd(a.sums_out + (int64_t)r * kSumSlots + copy * 8 + t,
+                  (unsigned long long)llrint(tot * (kSumScale * (double)a.C.C44)));
+    }
+    if (own) {
+        const float alpha4 = 0.25f * R.alpha * a.C.C44, beta = R.beta;
+#pragma unroll
+        for (int l = 0; l < TZ; ++l) {
+            if (TZ > 2 && z0 + l >= K) break;   // the last tile of an edge that TZ does not divide
+            float F[3];
+            pair_force<VX>(sPa[l], sPb[l], lx, ly, F);
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                const int64_t idx = j * P + own_n + (int64_t)KK * l;
+                const float wn = __builtin_fmaf(-alpha4, F[j], beta * wz[l][j]);
+                w[idx] = wn;
+                uout[idx] = uz[l][j] + wn;
+            }
+        }
+    }
+}
+
 // After a sequence's last step: the context's (E, wE), one block per replica.
 __global__ void k_seq_fold(double* state, const double* st_last, const unsigned long long* sums_last,
                            const RepDev* reps)
@@ -301,7 +453,7 @@ __global__ void k_seq_fold(double* state, const double* st_last, const unsigned 
     const int r = blockIdx.x, I = threadIdx.x;
     if (I >= 6) return;
     double E_I, wE_I;
-    advance_E(reps, r, st_last, kSeqState, sums_last, I, E_I, wE_I);
+    advance_E(reps[r], r, st_last, kSeqState, sums_last, I, E_I, wE_I);
     state[(int64_t)r * kStateDoubles + kE + I] = E_I;
     state[(int64_t)r * kStateDoubles + kWE + I] = wE_I;
 }
@@ -519,9 +671,20 @@ hipError_t seq_step(hmc_ctx_s* c, hipStream_t s, int i, const float* uin, float*
     a.tile_rep = c->d.tile_rep;
     a.order = c->block_order;
     a.plane = c->total_sites;
+    a.single = c->n_rep == 1;
+    a.K = c->reps[0].K;
+    a.tile_z = c->reps[0].tile_z;
+    a.alpha = c->reps[0].glob_alpha;
+    a.beta = c->reps[0].glob_beta;
     const int tok = s == c->stream ? prof_begin(c, kProfRefreshStep) : -1;
     const dim3 g(c->tile_blocks);
-    if (c->reps[0].tile_y == 32) {
+    if (c->flat_depth == 1) {
+        hipLaunchKernelGGL(k_global_step_flat<1>, g, dim3(kFlatThreads), 0, s, a);
+    } else if (c->flat_depth == 2) {
+        hipLaunchKernelGGL(k_global_step_flat<2>, g, dim3(kFlatThreads), 0, s, a);
+    } else if (c->flat_depth == 4) {
+        hipLaunchKernelGGL(k_global_step_flat<4>, g, dim3(kFlatThreads), 0, s, a);
+    } else if (c->reps[0].tile_y == 32) {
         if (c->step_streams)
             hipLaunchKernelGGL((k_global_step_tiled<32, true>), g, dim3(kTileX * 32), 0, s, a);
         else

@@ -45,6 +45,7 @@ constexpr int kPassSplitBelow = 1024;  // passes with fewer chunks run one site 
 constexpr int kMaxChunkBlocks = 8192;  // blocks per replica of node-parallel reductions
 constexpr int kTileX = 32, kTileY = 8;   // node tile of the explicit step in x, y
 constexpr int kTileZMax = 32;            // deepest tile in z (node layers per block)
+constexpr int kFlatDepth = 4;            // tiles up to this depth take k_global_step_flat
 
 // Work-groups are dispatched to the 8 XCDs round-robin by their index, and each XCD has its
 // own L2.  Launches whose neighbouring blocks share data (halo rows, neighbour planes) use
@@ -191,6 +192,8 @@ struct hmc_ctx_s {
     int node_blocks = 0;            // total blocks of node kernels
     int tile_blocks = 0;            // total blocks of the tiled explicit step
     bool step_streams = false;      // explicit step: own-node u and w read / written non-temporally
+    int flat_depth = 0;             // 1, 2 or 4: every replica's tiles are of this depth and the
+                                    // explicit step is k_global_step_flat
     bool elastic_buffers = false;
     bool have_orient = false, have_spins = false, have_load = false, have_stress = false;
     bool have_state = false;
