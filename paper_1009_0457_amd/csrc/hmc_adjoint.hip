@@ -16,10 +16,14 @@
 // term dU/dtheta_g += sum_{v in g} 1/2 eps_v . (dC_g/dtheta) eps_v; after step 0 the start
 // E_0 = mean(S_q) Sigma adds E^_0 . (n_g/K^3) (dS_g/dtheta) Sigma and mean(S) E^_0.
 //
-// The stiffness-derivative terms are contracted with the voxel's dC/dtheta (three angles)
-// as they arise and summed per voxel in FP64: G_v = 1/2 eps_n.dC eps_n - sum_t eta_t.dC eps_t;
-// per-grain sums of G use 64-bit fixed-point atomics (order-independent, so the result is
-// deterministic).  Forward states are recovered from checkpoints every `ckpt_every` steps
+// The stiffness-derivative terms are contracted as they arise and summed per voxel in FP64, as torques
+// about the lab axes: turning a crystal by dw turns its projectors, dP_a = [W, P_a], so that with
+// S(e) = (C11 - C12 - 2 C44) sum_a (P_a : e) P_a the change of eta.C eps is
+//     tr(W (X - X^T)),   X = S(eps) eta + S(eta) eps,
+// which needs no derivative table: G_v = 1/2 g(eps_n, eps_n) - sum_t g(eta_t, eps_t) with g the vector of
+// those changes per unit turn about x, y and z.  An Euler angle turns the crystal about its own axis
+// (z; the line of nodes; the crystal's z), along which G is taken at the end.  Per-grain sums use
+// 64-bit fixed-point atomics (order-independent, so the result is deterministic).  Forward states are recovered from checkpoints every `ckpt_every` steps
 // by recomputing one segment at a time.  The adjoint step is tiled like the forward step.
 #include <cmath>
 #include <cstring>
@@ -36,7 +40,7 @@ constexpr double kFixScale = 1099511627776.0;   // 2^40
 constexpr int kAdjSeq = 32;
 
 struct AdjLayout {
-    size_t ckpt, seg_u[2], seg_E[2], ub0, ub1, wb0, wb1, G, dC, dS, adj, asums, aseq, grad, total;
+    size_t ckpt, seg_u[2], seg_E[2], ub0, ub1, wb0, wb1, G, axes, low, dS, adj, asums, aseq, grad, total;
     int n_ck;          // checkpoints of segment starts
     size_t ck_bytes;   // bytes per checkpoint: u, w planes then 12 doubles
 };
@@ -68,7 +72,8 @@ static AdjLayout adj_layout(const hmc_ctx_s* c, int n_steps, int k)
     L.wb0 = take(3 * n3 * sizeof(float));
     L.wb1 = take(3 * n3 * sizeof(float));
     L.G = take(3 * n3 * sizeof(double));
-    L.dC = take(Q * 3 * kTab * sizeof(float));
+    L.axes = take(Q * 9 * sizeof(double));
+    L.low = take(Q * kProj * sizeof(float));
     L.dS = take(Q * 3 * kTab * sizeof(float));
     L.adj = take(64 * sizeof(double));
     L.asums = take(3 * kSumSlots * sizeof(unsigned long long));
@@ -113,25 +118,57 @@ __device__ __forceinline__ void adj_store(double* dst, int I, const double v[5])
     dst[kWEt + I] = v[4];
 }
 
-// eta . (dC_q eps) for the three angles q of grain g
-__device__ __forceinline__ void angle_contractions(const float* __restrict__ dC, int g, const float eta[6],
-                                                  const float eps[6], double out[3])
+// The part of a cubic stress that turns with the crystal (a multiple of 1 commutes with every strain):
+// q1 c1 + q2 c2 of cubic_stress, in units of C44 and FP64, with `l` what the rounding of the rows c left: turned,
+// that rounding moves a torque by 5.4e-8 of its norm over random orientations (three tables of rounded
+// derivatives: 2.5e-8).
+__device__ __forceinline__ void turning_stress(const float c[kProjUsed], const float l[kProjUsed], float sgn,
+                                               const float e[6], double s[6])
 {
+    double d[kProjUsed];
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        float d6[6];
-        symv21(dC + ((int64_t)g * 3 + q) * kTab, eps, d6);
-        double v = 0.0;
+    for (int i = 0; i < kProjUsed; ++i) d[i] = (double)c[i] + (double)l[i];
+    double p1 = d[0] * e[0], p2 = d[6] * e[0];
 #pragma unroll
-        for (int I = 0; I < 6; ++I) v += (double)eta[I] * (double)d6[I];
-        out[q] = v;
+    for (int I = 1; I < 6; ++I) {
+        p1 = fma(d[I], (double)e[I], p1);
+        p2 = fma(d[6 + I], (double)e[I], p2);
     }
+    const double q1 = sgn * fma(2.0, p1, p2), q2 = sgn * fma(2.0, p2, p1);
+#pragma unroll
+    for (int I = 0; I < 6; ++I) s[I] = fma(q2, d[6 + I], q1 * d[I]);
+}
+
+// m += (the vector of) S H - H S for a stress S and a strain H (engineering shears): the entries
+// (y, z), (z, x) and (x, y).
+__device__ __forceinline__ void add_commutator(const double S[6], const float e[6], double m[3])
+{
+    const double S0 = S[0], S1 = S[1], S2 = S[2], S3 = S[3], S4 = S[4], S5 = S[5];
+    const double H0 = e[0], H1 = e[1], H2 = e[2], H3 = 0.5 * (double)e[3], H4 = 0.5 * (double)e[4],
+                 H5 = 0.5 * (double)e[5];
+    m[0] += S5 * H4 - S4 * H5 + (S1 - S2) * H3 + S3 * (H2 - H1);
+    m[1] += S3 * H5 - S5 * H3 + (S2 - S0) * H4 + S4 * (H0 - H2);
+    m[2] += S4 * H3 - S3 * H4 + (S0 - S1) * H5 + S5 * (H1 - H0);
+}
+
+// g = the changes of eta.C eps / C44 per unit turn of the crystal about x, y and z.
+__device__ __forceinline__ void turning_work(const float c[kProjUsed], const float l[kProjUsed], float sgn,
+                                             const float eta[6], const float eps[6], double g[3])
+{
+    double s[6];
+    double m[3] = {0.0, 0.0, 0.0};
+    turning_stress(c, l, sgn, eps, s);
+    add_commutator(s, eta, m);
+    turning_stress(c, l, sgn, eta, s);
+    add_commutator(s, eps, m);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) g[k] = 2.0 * m[k];
 }
 
 struct AdjInitArgs {
     const int16_t* spins;
-    const float* Ctab;
-    const float* dC;
+    CubicTab C;
+    const float* low;        // Q x kProj: what the rounding of C's rows left
     const float* u;
     float* ub;
     float* wb;
@@ -142,7 +179,9 @@ struct AdjInitArgs {
     int64_t n3;
 };
 
-// Final-state adjoint: u^_n = sum_v B_v^T sigma_v, G_v = 1/2 eps.dC eps, partial sums of sigma.
+// Final-state adjoint, with the stress of the steps (another rounding of the stiffness would leave forces
+// that the final state does not have): u^_n = sum_v B_v^T sigma_v, G_v = 1/2 g(eps, eps) (in units of C44), partial sums
+// of sigma.
 __global__ __launch_bounds__(256) void k_adj_init(AdjInitArgs a)
 {
     const int K = a.K;
@@ -160,23 +199,27 @@ __global__ __launch_bounds__(256) void k_adj_init(AdjInitArgs a)
             float e[6], s[6];
             voxel_strain(a.u, a.n3, K, vx, vy, vz, E, e);
             const int g = a.spins[vx + (int64_t)K * (vy + (int64_t)K * vz)];
-            symv21(a.Ctab + (int64_t)g * kTab, e, s);
+            float row[kProjUsed];
+            cubic_row(a.C.P, g, row);
+            cubic_stress(row, a.C, e, s);
             const float sx = ca ? 0.25f : -0.25f, sy = cb ? 0.25f : -0.25f, sz = cc ? 0.25f : -0.25f;
             f[0] += sx * s[0] + sy * s[5] + sz * s[4];
             f[1] += sx * s[5] + sy * s[1] + sz * s[3];
             f[2] += sx * s[4] + sy * s[3] + sz * s[2];
             if (c == 0) {
 #pragma unroll
-                for (int I = 0; I < 6; ++I) acc[I] += (double)s[I];
+                for (int I = 0; I < 6; ++I) acc[I] += a.C.C44 * (double)s[I];
+                float low[kProjUsed];
                 double gq[3];
-                angle_contractions(a.dC, g, e, e, gq);
+                cubic_row(a.low, g, low);
+                turning_work(row, low, a.C.sgn, e, e, gq);
 #pragma unroll
                 for (int q = 0; q < 3; ++q) a.G[(int64_t)q * a.n3 + n] = 0.5 * gq[q];
             }
         }
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-            a.ub[(int64_t)j * a.n3 + n] = f[j];
+            a.ub[(int64_t)j * a.n3 + n] = (float)(a.C.C44 * f[j]);
             a.wb[(int64_t)j * a.n3 + n] = 0.f;
         }
     }
@@ -185,8 +228,8 @@ __global__ __launch_bounds__(256) void k_adj_init(AdjInitArgs a)
 
 struct AdjStepArgs {
     const int16_t* spins;
-    const float* Ctab;
-    const float* dC;         // Q x 3 x kTab
+    CubicTab C;
+    const float* low;        // Q x kProj: what the rounding of C's rows left
     const float* ub_in;
     float* ub_out;
     const float* wb_in;      // read at neighbour nodes: ping-pong like ub
@@ -199,36 +242,32 @@ struct AdjStepArgs {
     unsigned long long* sums_out;        // this step's
     unsigned long long* sums_clear;      // the next step's, cleared by block 0
     double* G;               // 3 planes
-    const RepDev* reps;
+    int K, tile_z;
     float alpha, beta;
     double betaE, alphaE;
     int order;               // logical block order (hmc_set_block_order)
 };
 
-// tau = C_q eta and, where `owned`, gq_k = eta . (dC_{q,k} eps) for the three angles k,
-// with the tables of a wavefront's first two grains from scalar loads;
-// wavefronts with more grains gather per lane.
-__device__ __forceinline__ void adjoint_voxel(const float* Ctab, const float* dC, int q, bool owned,
-                                              const float eta[6], const float eps[6], float tau[6], double gq[3])
+// tau = C eta / C44 and, where `owned`, the turning work, for a wavefront's voxels: of one grain with its rows
+// from scalar loads, of several with each lane gathering its own.
+__device__ __forceinline__ void adjoint_voxel(const CubicTab& T, const float* low, int q, bool owned,
+                                              const float eta[6], const float eps[6], float tau[6], double g[3])
 {
-    auto with_rows = [&](int g) {   // g is the same in every active lane
-        float c[21];
-        uniform_row(Ctab, g, c);
-        symv21(c, eta, tau);
-        if (owned) angle_contractions(dC, g, eta, eps, gq);
-    };
     const int q0 = __builtin_amdgcn_readfirstlane(q);
-    const uint64_t other = __builtin_amdgcn_ballot_w64(q != q0);
-    if (other == 0) {
-        with_rows(q0);
+    float c[kProjUsed], l[kProjUsed];
+    if (__builtin_amdgcn_ballot_w64(q != q0) == 0) {
+        uniform_cubic_row(T.P, q0, c);
+        cubic_stress(c, T, eta, tau);
+        if (owned) {
+            uniform_cubic_row(low, q0, l);
+            turning_work(c, l, T.sgn, eta, eps, g);
+        }
     } else {
-        const int q1 = __builtin_amdgcn_readlane(q, (int)__builtin_ctzll(other));
-        if (__builtin_amdgcn_ballot_w64(q != q0 && q != q1) == 0) {
-            with_rows(q0);
-            if (q == q1) with_rows(q1);
-        } else {
-            symv21(Ctab + (int64_t)q * kTab, eta, tau);
-            if (owned) angle_contractions(dC, q, eta, eps, gq);
+        cubic_row(T.P, q, c);
+        cubic_stress(c, T, eta, tau);
+        if (owned) {
+            cubic_row(low, q, l);
+            turning_work(c, l, T.sgn, eta, eps, g);
         }
     }
 }
@@ -237,8 +276,13 @@ __device__ __forceinline__ void adjoint_voxel(const float* Ctab, const float* dC
 // sums of the nodal fields and of the voxel stresses in LDS, previous layer in registers):
 // the nodal field a = alpha (w^ + u^) and the forward displacement u_t give each voxel its
 // adjoint strain eta and forward strain eps; tau = C eta is formed once per tile, and the
-// voxels the block owns also add their angle contractions to G and tau to the block's sums.
-__global__ __launch_bounds__(256, 3) void k_adj_step(AdjStepArgs a)
+// voxels the block owns also add their torques to G (by an atomic nobody waits for: only this voxel's thread
+// adds to an entry, so the order of the sum is the steps') and tau to the block's sums.  Bound by VALU and
+// LDS work (64^3: 38 % of the issue slots, 84 B of fields a node, from L2), so the torque counts:
+// against three FP64 contractions with tables of 21 derivatives a grain it takes a backward step, forward
+// recompute included, from 27.4 to 23.0 us at 64^3, 52.7 to 50.8 at 80^3 and 78.6 to 57.1 at 96^3.  Two wavefronts a SIMD (185
+// registers) rather than three with spills: 22.8 against 23.9 us.
+__global__ __launch_bounds__(256, 2) void k_adj_step(AdjStepArgs a)
 {
     constexpr int NX = kTileX + 2, NY = kTileY + 2, VX = kTileX + 1, VY = kTileY + 1;
     constexpr int NP = (NX * NY + 255) / 256, VP = (kStepVox + 255) / 256;
@@ -246,10 +290,9 @@ __global__ __launch_bounds__(256, 3) void k_adj_step(AdjStepArgs a)
     __shared__ float2 sAb[NY][NX], sUb[NY][NX];
     __shared__ float4 sPa[VY][VX], sPb[VY][VX];
 
-    const RepDev R = a.reps[0];
-    const int K = R.K;
-    const int64_t n3 = R.n3;
-    const int ntx = (K + kTileX - 1) / kTileX, nty = (K + kTileY - 1) / kTileY, tz = R.tile_z;
+    const int K = a.K;
+    const int64_t n3 = (int64_t)K * K * K;
+    const int ntx = (K + kTileX - 1) / kTileX, nty = (K + kTileY - 1) / kTileY, tz = a.tile_z;
     const int lb = logical_block((int)blockIdx.x, (int)gridDim.x, a.order);
     int b = lb;
     const int bx = b % ntx;
@@ -354,7 +397,7 @@ __global__ __launch_bounds__(256, 3) void k_adj_step(AdjStepArgs a)
         float eta[6], eps[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         pair_strain<NX>(sAa, sAb, ix, iy, b3, eta);
         if (owned) pair_strain<NX>(sUa, sUb, ix, iy, E, eps);
-        adjoint_voxel(a.Ctab, a.dC, q, owned, eta, eps, tau, gq);
+        adjoint_voxel(a.C, a.low, q, owned, eta, eps, tau, gq);
     };
 
     // prologue: node layers z0-1, z0 -> voxel layer z0-1 (kept in registers)
@@ -365,7 +408,8 @@ __global__ __launch_bounds__(256, 3) void k_adj_step(AdjStepArgs a)
     store_pair();
     __syncthreads();
 #pragma unroll
-    for (int I = 0; I < 6; ++I) b3[I] = (float)(sb[I] * inv_n3);
+    for (int I = 0; I < 6; ++I)   // the same in every lane: kept in scalar registers
+        b3[I] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int((float)(sb[I] * inv_n3))));
     float tprev[VP][6];
 #pragma unroll
     for (int k = 0; k < VP; ++k)
@@ -385,14 +429,8 @@ __global__ __launch_bounds__(256, 3) void k_adj_step(AdjStepArgs a)
             sp_cur[k] = sp[k];
             asm volatile("" ::"v"(sp_cur[k]));   // take them before the loads below are issued
         }
-        // requested in the order needed: this layer's G of the owned voxels, the own nodes'
-        // w^ and u^, then the next layer's grains
+        // requested in the order needed: the own nodes' w^ and u^, then the next layer's grains
         const int64_t zoff = (int64_t)K * K * z;
-        double Gv[3] = {0.0, 0.0, 0.0};
-        if (vox_own[0]) {
-#pragma unroll
-            for (int qa = 0; qa < 3; ++qa) Gv[qa] = a.G[(int64_t)qa * n3 + vox_xy[0] + zoff];
-        }
         float wn_in[3] = {0.f, 0.f, 0.f}, un_in[3] = {0.f, 0.f, 0.f};
         const int64_t n = nx + (int64_t)K * ny + zoff;
         if (own) {
@@ -421,24 +459,172 @@ __global__ __launch_bounds__(256, 3) void k_adj_step(AdjStepArgs a)
 #pragma unroll
                 for (int I = 0; I < 6; ++I) acc[I] += (double)tau[I];
 #pragma unroll
-                for (int qa = 0; qa < 3; ++qa) a.G[(int64_t)qa * n3 + vox_xy[k] + zoff] = Gv[qa] - gq[qa];
+                for (int qa = 0; qa < 3; ++qa) unsafeAtomicAdd(&a.G[(int64_t)qa * n3 + vox_xy[k] + zoff], -gq[qa]);
             }
         }
         __syncthreads();                         // the voxel pair is complete
         if (own) {
+            const float quarter = (float)(0.25 * a.C.C44);
             float F[3];
             pair_force<VX>(sPa, sPb, lx, ly, F);
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
                 const int64_t idx = (int64_t)j * n3 + n;
-                a.ub_out[idx] = un_in[j] - 0.25f * F[j];
+                a.ub_out[idx] = un_in[j] - quarter * F[j];
                 a.wb_out[idx] = beta * (wn_in[j] + un_in[j]);
             }
         }
     }
     const double tot = block_total<6>(acc);
     if (threadIdx.x < 6)
-        atomicAdd(a.sums_out + (lb & (kSumCopies - 1)) * 8 + threadIdx.x, (unsigned long long)llrint(tot * kSumScale));
+        atomicAdd(a.sums_out + (lb & (kSumCopies - 1)) * 8 + threadIdx.x,
+                  (unsigned long long)llrint(tot * (kSumScale * a.C.C44)));
+}
+
+// The adjoint step for tiles of depth 1, laid out as k_global_step_flat: every load at once, a thread a
+// node column, a voxel column and an own-node column.  It serves the sizes whose blocks of one layer are
+// all resident at once, where a step is one chain of loads and barriers: forward recompute and adjoint step
+// together 10.8 -> 9.7 us at 16^3 and 11.3 -> 10.0 at 32^3 against k_adj_step.  From depth 2 on the
+// halo's projector rows and three fields a layer cost more than the shorter chain saves (64^3: 18.0 us
+// against 14.7), and k_adj_step is taken.
+__global__ __launch_bounds__(kFlatThreads, 3) void k_adj_flat(AdjStepArgs a)
+{
+    constexpr int TZ = 1;
+    constexpr int NX = kTileX + 2, NY = kTileY + 2, VX = kTileX + 1, VY = kTileY + 1;
+    __shared__ float4 sAa[TZ + 1][NY][NX], sUa[TZ + 1][NY][NX];
+    __shared__ float2 sAb[TZ + 1][NY][NX], sUb[TZ + 1][NY][NX];
+    __shared__ float4 sPa[TZ][VY][VX], sPb[TZ][VY][VX];
+    __shared__ double sb[6], red[6][4];
+
+    const int K = a.K, KK = K * K;
+    const int64_t n3 = (int64_t)KK * K;
+    const int ntx = (K + kTileX - 1) / kTileX, nty = (K + kTileY - 1) / kTileY;
+    const int lb = logical_block((int)blockIdx.x, (int)gridDim.x, a.order);
+    int b = lb;
+    const int bx = b % ntx;
+    b /= ntx;
+    const int by = b % nty, bz = b / nty;
+    const int x0 = bx * kTileX, y0 = by * kTileY, z0 = bz * TZ;
+    const int t = threadIdx.x;
+
+    int vx, vy;
+    step_voxel_pos(t, vx, vy);
+    const bool vox = t < kStepVox;
+    const bool owned = vox && vx >= 1 && vy >= 1 && x0 - 1 + vx < K && y0 - 1 + vy < K;
+    const int vox_xy = wrap_tile(x0 - 1 + vx, K) + K * wrap_tile(y0 - 1 + vy, K);
+    int sp[TZ + 1];
+#pragma unroll
+    for (int l = 0; l <= TZ; ++l) sp[l] = a.spins[vox_xy + (int64_t)KK * wrap_once(z0 - 1 + l, K)];
+    const int ix = t % NX, iy = t / NX;
+    const bool node = t < NX * NY;
+    const int node_xy = wrap_tile(x0 - 1 + ix, K) + K * wrap_tile(y0 - 1 + iy, K);
+    float wn[TZ + 2][3], bn[TZ + 2][3], un[TZ + 2][3];
+#pragma unroll
+    for (int l = 0; l < TZ + 2; ++l) {
+        const int64_t n = node_xy + (int64_t)KK * wrap_once(z0 - 1 + l, K);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            wn[l][j] = a.wb_in[j * n3 + n];
+            bn[l][j] = a.ub_in[j * n3 + n];
+            un[l][j] = a.u_t[j * n3 + n];
+        }
+    }
+    const int lx = t % kTileX, ly = t / kTileX;
+    const bool own = t < kTileX * kTileY && x0 + lx < K && y0 + ly < K;
+    const int64_t own_n = own ? x0 + lx + (int64_t)K * (y0 + ly) + (int64_t)KK * z0 : 0;
+    double Et[6];
+#pragma unroll
+    for (int I = 0; I < 6; ++I) Et[I] = a.E_t[I];
+    float wo[TZ][3], uo[TZ][3];
+#pragma unroll
+    for (int l = 0; l < TZ; ++l)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            wo[l][j] = a.wb_in[j * n3 + own_n + (int64_t)KK * l];
+            uo[l][j] = a.ub_in[j * n3 + own_n + (int64_t)KK * l];
+        }
+    if (t >= kFlatThreads - 64 && t < kFlatThreads - 64 + 6) {   // the last wavefront has no voxels
+        const int I = t - (kFlatThreads - 64);
+        double v[5];
+        adj_advance(a.st_in, a.sums_in, I, a.betaE, a.alphaE, v);
+        sb[I] = v[2];
+        if (lb == 0) adj_store(a.st_out, I, v);
+    }
+    if (lb == 0 && t < kSumSlots) a.sums_clear[t] = 0ull;
+    float c[TZ + 1][kProjUsed];
+#pragma unroll
+    for (int l = 0; l <= TZ; ++l) cubic_row(a.C.P, sp[l], c[l]);
+    float low[kProjUsed];
+    cubic_row(a.low, sp[1], low);
+    if (node) {
+#pragma unroll
+        for (int l = 0; l < TZ + 2; ++l)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) wn[l][j] = a.alpha * (wn[l][j] + bn[l][j]);
+#pragma unroll
+        for (int l = 0; l <= TZ; ++l) {
+            pair_node_entry(wn[l + 1], wn[l], sAa[l][iy][ix], sAb[l][iy][ix]);
+            pair_node_entry(un[l + 1], un[l], sUa[l][iy][ix], sUb[l][iy][ix]);
+        }
+    }
+    __syncthreads();
+    double acc[6] = {0, 0, 0, 0, 0, 0};
+    if (vox) {
+        const double inv_n3 = 1.0 / (double)n3;
+        float b3[6], E[6], tau[2][6];
+#pragma unroll
+        for (int I = 0; I < 6; ++I) {
+            b3[I] = (float)(sb[I] * inv_n3);
+            E[I] = (float)Et[I];
+        }
+#pragma unroll
+        for (int l = 0; l <= TZ; ++l) {
+            float eta[6], eps[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            double g[3];
+            const bool add = owned && l > 0;
+            pair_strain<NX>(sAa[l], sAb[l], vx, vy, b3, eta);
+            if (add) pair_strain<NX>(sUa[l], sUb[l], vx, vy, E, eps);
+            cubic_stress(c[l], a.C, eta, tau[l & 1]);
+            if (add) turning_work(c[l], low, a.C.sgn, eta, eps, g);
+            if (l > 0) {
+                pair_voxel_entry(tau[l & 1], tau[(l & 1) ^ 1], sPa[l - 1][vy][vx], sPb[l - 1][vy][vx]);
+                if (add) {
+#pragma unroll
+                    for (int I = 0; I < 6; ++I) acc[I] += (double)tau[l & 1][I];
+#pragma unroll
+                    for (int k = 0; k < 3; ++k)
+                        unsafeAtomicAdd(&a.G[k * n3 + vox_xy + (int64_t)KK * (z0 + l - 1)], -g[k]);
+                }
+            }
+        }
+    }
+    if (t < kTileX * kTileY) {   // whole wavefronts; the halo's voxels (the others) are not owned
+#pragma unroll
+        for (int I = 0; I < 6; ++I) {
+            const double v = wave_sum(acc[I]);
+            if ((t & 63) == 0) red[I][t >> 6] = v;
+        }
+    }
+    __syncthreads();
+    if (t < 6) {
+        const double tot = (red[t][0] + red[t][1]) + (red[t][2] + red[t][3]);
+        atomicAdd(a.sums_out + (lb & (kSumCopies - 1)) * 8 + t,
+                  (unsigned long long)llrint(tot * (kSumScale * a.C.C44)));
+    }
+    if (own) {
+        const float quarter = (float)(0.25 * a.C.C44);
+#pragma unroll
+        for (int l = 0; l < TZ; ++l) {
+            float F[3];
+            pair_force<VX>(sPa[l], sPb[l], lx, ly, F);
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                const int64_t idx = j * n3 + own_n + (int64_t)KK * l;
+                a.ub_out[idx] = uo[l][j] - quarter * F[j];
+                a.wb_out[idx] = a.beta * (wo[l][j] + uo[l][j]);
+            }
+        }
+    }
 }
 
 // After the last adjoint step: the adjoint state block.
@@ -477,6 +663,7 @@ struct AdjGradArgs {
     const float* Stab;
     const float* dS;    // Q x 3 x kTab
     const double* G;
+    const double* axes; // Q x 3 x 3: the axis each Euler angle turns the grain about, times C44
     const double* adj;  // E^_0 at kEb
     double Sigma[6];
     unsigned long long* grad;   // Q x 3 fixed point
@@ -484,7 +671,7 @@ struct AdjGradArgs {
     int64_t n3;
 };
 
-// Per voxel: the three stiffness-angle sums G_v plus the start-strain term
+// Per voxel: the stiffness sums G_v along the three angles' axes plus the start-strain term
 // (1/K^3) E^_0 . dS Sigma into its grain (fixed-point atomics); partial sums of S E^_0.
 __global__ __launch_bounds__(256) void k_adj_grad(AdjGradArgs a)
 {
@@ -499,10 +686,14 @@ __global__ __launch_bounds__(256) void k_adj_grad(AdjGradArgs a)
     double acc[6] = {0, 0, 0, 0, 0, 0};
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < a.n3; v += (int64_t)gridDim.x * blockDim.x) {
         const int g = a.spins[v];
+        double G[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) G[k] = a.G[(int64_t)k * a.n3 + v];
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
             const float* ds = a.dS + ((int64_t)g * 3 + q) * kTab;
-            double val = a.G[(int64_t)q * a.n3 + v];
+            const double* ax = a.axes + (int64_t)g * 9 + 3 * q;
+            double val = ax[0] * G[0] + ax[1] * G[1] + ax[2] * G[2];
             int k = 0;
 #pragma unroll
             for (int I = 0; I < 6; ++I)
@@ -666,7 +857,8 @@ hmc_status hmc_elastic_backward(hmc_ctx c, void* ws, size_t bytes, double dU, do
     float* ub[2] = {(float*)(base + L.ub0), (float*)(base + L.ub1)};
     float* wb[2] = {(float*)(base + L.wb0), (float*)(base + L.wb1)};
     double* G = (double*)(base + L.G);
-    float* dC = (float*)(base + L.dC);
+    double* axes = (double*)(base + L.axes);
+    float* low = (float*)(base + L.low);
     float* dS = (float*)(base + L.dS);
     double* adj = (double*)(base + L.adj);
     unsigned long long* asums = (unsigned long long*)(base + L.asums);
@@ -676,19 +868,27 @@ hmc_status hmc_elastic_backward(hmc_ctx c, void* ws, size_t bytes, double dU, do
 
     // per-grain derivative tables
     {
-        std::vector<float> hC((size_t)Q * 3 * kTab, 0.f), hS((size_t)Q * 3 * kTab, 0.f);
-        std::vector<double> dCd((size_t)Q * 108), dSd((size_t)Q * 108);
+        std::vector<float> hS((size_t)Q * 3 * kTab, 0.f), hl((size_t)Q * kProj, 0.f);
+        std::vector<double> dCd((size_t)Q * 108), dSd((size_t)Q * 108), ax((size_t)Q * 9);
         if (hmc_grain_table_derivatives(c->euler.data(), Q, c->p.C11, c->p.C12, c->p.C44, dCd.data(), dSd.data()) !=
             HMC_OK)
             return afail(c, HMC_ENUMERIC, "orientation derivatives");
-        for (int g = 0; g < Q; ++g)
+        for (int g = 0; g < Q; ++g) {
             for (int q = 0; q < 3; ++q)
                 for (int i = 0; i < 6; ++i)
-                    for (int j = i; j < 6; ++j) {
-                        hC[((size_t)g * 3 + q) * kTab + sym_index(i, j)] = (float)dCd[(size_t)g * 108 + q * 36 + 6 * i + j];
+                    for (int j = i; j < 6; ++j)
                         hS[((size_t)g * 3 + q) * kTab + sym_index(i, j)] = (float)dSd[(size_t)g * 108 + q * 36 + 6 * i + j];
-                    }
-        ATRY(hipMemcpyAsync(dC, hC.data(), hC.size() * sizeof(float), hipMemcpyHostToDevice, c->stream), "backward");
+            // phi1 turns about z, Phi about the line of nodes Rz(phi1) x, phi2 about the crystal's z
+            const double* e = &c->euler[3 * (size_t)g];
+            const double n[9] = {0.0, 0.0, 1.0, std::cos(e[0]), std::sin(e[0]), 0.0,
+                                 std::sin(e[0]) * std::sin(e[1]), -std::cos(e[0]) * std::sin(e[1]), std::cos(e[1])};
+            for (int k = 0; k < 9; ++k) ax[(size_t)g * 9 + k] = c->p.C44 * n[k];
+            double proj[kProjUsed];
+            axis_projectors(e, c->p.C11, c->p.C12, c->p.C44, proj);
+            for (int k = 0; k < kProjUsed; ++k) hl[(size_t)g * kProj + k] = (float)(proj[k] - (double)(float)proj[k]);
+        }
+        ATRY(hipMemcpyAsync(low, hl.data(), hl.size() * sizeof(float), hipMemcpyHostToDevice, c->stream), "backward");
+        ATRY(hipMemcpyAsync(axes, ax.data(), ax.size() * sizeof(double), hipMemcpyHostToDevice, c->stream), "backward");
         ATRY(hipMemcpyAsync(dS, hS.data(), hS.size() * sizeof(float), hipMemcpyHostToDevice, c->stream), "backward");
         ATRY(hipMemsetAsync(grad, 0, (size_t)Q * 3 * sizeof(unsigned long long), c->stream), "backward");
         ATRY(hipStreamSynchronize(c->stream), "backward");
@@ -699,7 +899,7 @@ hmc_status hmc_elastic_backward(hmc_ctx c, void* ws, size_t bytes, double dU, do
     if (st != HMC_OK) return st;
     c->cur_u = 0;
     {
-        AdjInitArgs a{c->d.spins, c->d.Ctab, dC, c->d.u[0], ub[0], wb[0], G, c->d.partials, c->d.state, R.K, n3};
+        AdjInitArgs a{c->d.spins, cubic_tab(c), low, c->d.u[0], ub[0], wb[0], G, c->d.partials, c->d.state, R.K, n3};
         hipLaunchKernelGGL(k_adj_init, dim3(nb), dim3(256), 0, c->stream, a);
         hipLaunchKernelGGL(k_adj_E, dim3(1), dim3(256), 0, c->stream, adj, c->d.partials, nb, R.glob_alphaE);
         ATRY(hipGetLastError(), "backward: start");
@@ -708,6 +908,8 @@ hmc_status hmc_elastic_backward(hmc_ctx c, void* ws, size_t bytes, double dU, do
     // the first adjoint step adds into tau-sum buffer 0 (2 uint32 per 64-bit word)
     ATRY(launch_fill_u32((uint32_t*)asums, 0u, 2 * kSumSlots, c->stream), "backward: start");
     const int n_seg = (n + k - 1) / k;
+    // tiles as deep as the forward step's (72^3, depth 4: 33.1 us a step with the recompute, 36.5 at 2)
+    const int adj_depth = R.tile_z;
     // Segment j's forward states are recomputed from its checkpoint into buffer j & 1.  With
     // the auxiliary stream the recomputation of segment j-1 runs while the context's stream
     // takes segment j's adjoint steps (both are latency-bound at this size); events order
@@ -762,8 +964,8 @@ hmc_status hmc_elastic_backward(hmc_ctx c, void* ws, size_t bytes, double dU, do
         for (int t = t1 - 1; t >= t0; --t) {
             AdjStepArgs a;
             a.spins = c->d.spins;
-            a.Ctab = c->d.Ctab;
-            a.dC = dC;
+            a.C = cubic_tab(c);
+            a.low = low;
             a.ub_in = ub[cur_b];
             a.ub_out = ub[1 - cur_b];
             a.wb_in = wb[cur_b];
@@ -776,7 +978,8 @@ hmc_status hmc_elastic_backward(hmc_ctx c, void* ws, size_t bytes, double dU, do
             a.sums_out = asums + (i_adj % 3) * kSumSlots;
             a.sums_clear = asums + ((i_adj + 1) % 3) * kSumSlots;
             a.G = G;
-            a.reps = c->d.reps;
+            a.K = R.K;
+            a.tile_z = adj_depth;
             a.alpha = R.glob_alpha;
             a.beta = R.glob_beta;
             a.betaE = (double)R.glob_beta;
@@ -784,7 +987,11 @@ hmc_status hmc_elastic_backward(hmc_ctx c, void* ws, size_t bytes, double dU, do
             a.order = c->block_order;
             const int tok = prof_begin(c, kProfRefreshStep);
             // the adjoint step keeps 32 x 8 tiles whatever the forward step's rows
-            hipLaunchKernelGGL(k_adj_step, dim3(tile_blocks_of(R.K, R.tile_z, kTileY)), dim3(256), 0, c->stream, a);
+            const dim3 grid(tile_blocks_of(R.K, adj_depth, kTileY));
+            if (adj_depth == 1)
+                hipLaunchKernelGGL(k_adj_flat, grid, dim3(kFlatThreads), 0, c->stream, a);
+            else
+                hipLaunchKernelGGL(k_adj_step, grid, dim3(256), 0, c->stream, a);
             prof_end(c, tok);
             ATRY(hipGetLastError(), "backward: step");
             cur_b = 1 - cur_b;
@@ -802,6 +1009,7 @@ hmc_status hmc_elastic_backward(hmc_ctx c, void* ws, size_t bytes, double dU, do
         a.Stab = c->d.Stab;
         a.dS = dS;
         a.G = G;
+        a.axes = axes;
         a.adj = adj;
         for (int I = 0; I < 6; ++I) a.Sigma[I] = R.Sigma[I];
         a.grad = grad;

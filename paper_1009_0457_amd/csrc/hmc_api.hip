@@ -281,17 +281,6 @@ void grain_tables(const double e[3], double C11, double C12, double C44, double 
         }
 }
 
-// The projectors on the first two crystal axes, times sqrt(|C11 - C12 - 2 C44| / C44) (kProj).
-void axis_projectors(const double e[3], double C11, double C12, double C44, float P[kProjUsed])
-{
-    const double sa = std::sqrt(std::fabs(C11 - C12 - 2.0 * C44) / C44);
-    static const int pi[6] = {0, 1, 2, 1, 0, 0}, pj[6] = {0, 1, 2, 2, 2, 1};
-    double A[3][3];
-    bunge(e, A);
-    for (int m = 0; m < 2; ++m)
-        for (int I = 0; I < 6; ++I) P[6 * m + I] = (float)(sa * A[pi[I]][m] * A[pj[I]][m]);
-}
-
 // Derivatives of the lab tables with respect to the three Euler angles (phi1, Phi, phi2):
 // dA by differentiating one factor of Rz(phi1) Rx(Phi) Rz(phi2), then the product rule on
 // the quadratic transformation entries and on C' = T C T^T, S' = N S N^T.
@@ -716,7 +705,9 @@ hmc_status upload_tables(hmc_ctx c, int rep, const double* euler)
                 Ct[(size_t)g * kTab + sym_index(i, j)] = (float)Cl[6 * i + j];
                 St[(size_t)g * kTab + sym_index(i, j)] = (float)Sl[6 * i + j];
             }
-        axis_projectors(euler + 3 * g, c->p.C11, c->p.C12, c->p.C44, &Pt[(size_t)g * kProj]);
+        double proj[kProjUsed];
+        axis_projectors(euler + 3 * g, c->p.C11, c->p.C12, c->p.C44, proj);
+        for (int i = 0; i < kProjUsed; ++i) Pt[(size_t)g * kProj + i] = (float)proj[i];
     }
     if (c->elastic_buffers)
         HMC_TRY(c, hipMemcpyAsync(c->d.Ptab + R.grain_off * kProj, Pt.data(), Pt.size() * sizeof(float),
@@ -816,6 +807,18 @@ bool bad_rep(hmc_ctx c, int32_t r) { return r < 0 || r >= c->n_rep; }
 // kernel timing hooks
 // ------------------------------------------------------------------------------------
 namespace hmc {
+
+// The projectors on the first two crystal axes, less a third of 1 each, times
+// sqrt(|C11 - C12 - 2 C44| / C44) (kProj).
+void axis_projectors(const double e[3], double C11, double C12, double C44, double P[kProjUsed])
+{
+    const double sa = std::sqrt(std::fabs(C11 - C12 - 2.0 * C44) / C44);
+    static const int pi[6] = {0, 1, 2, 1, 0, 0}, pj[6] = {0, 1, 2, 2, 2, 1};
+    double A[3][3];
+    bunge(e, A);
+    for (int m = 0; m < 2; ++m)
+        for (int I = 0; I < 6; ++I) P[6 * m + I] = sa * (A[pi[I]][m] * A[pj[I]][m] - (I < 3 ? 1.0 / 3.0 : 0.0));
+}
 
 static hipEvent_t take_event(hmc_ctx_s* c)
 {

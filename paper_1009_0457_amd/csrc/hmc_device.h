@@ -1,6 +1,8 @@
 // hmc_device.h -- device helpers shared by the global-solve and adjoint kernels.
 #pragma once
 
+#include <cmath>
+
 #include "hmc_internal.h"
 
 namespace hmc {
@@ -17,6 +19,9 @@ __device__ __forceinline__ int wrap_tile(int a, int K)
     return a < K ? a : a % K;
 }
 
+// The same for -K <= a < 2K.
+__device__ __forceinline__ int wrap_once(int a, int K) { return a < 0 ? a + K : (a < K ? a : a - K); }
+
 template <class Tab>
 __device__ __forceinline__ void symv21(Tab c, const float e[6], float s[6])
 {
@@ -28,35 +33,39 @@ __device__ __forceinline__ void symv21(Tab c, const float e[6], float s[6])
     s[5] = c[5] * e[0] + c[10] * e[1] + c[14] * e[2] + c[17] * e[3] + c[19] * e[4] + c[20] * e[5];
 }
 
-// The 21 entries of grain q's table when q is the same in every active lane (e.g. from
-// readfirstlane), read through the scalar data cache: the constant address space lets the
-// compiler use scalar loads, which leave the vector memory path (and its in-order wait
-// counter) to the field data.  Tables are read-only while any kernel that reads them runs.
+// Read-only device memory read at a wave-uniform address: the constant address space lets the compiler
+// use scalar loads, which leave the vector memory path (and its in-order wait counter) to the field
+// data.  Tables are read-only while any kernel that reads them runs.
 typedef const __attribute__((address_space(4))) float* UniformTab;
-__device__ __forceinline__ void uniform_row(const float* tab, int q, float c[21])
-{
-    const UniformTab u = (UniformTab)(tab + (int64_t)q * kTab);
-#pragma unroll
-    for (int i = 0; i < 21; ++i) c[i] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(u[i])));
-}
 
 // The stiffness of cubic crystals by grain, in units of C44: with an = (C11 - C12 - 2 C44) / C44 and
-// the projectors P1, P2, P3 on the crystal axes (P1 + P2 + P3 = 1),
-//     C e / C44 = lam tr(e) 1 + 2 e + an sum_a (P_a : e) P_a,   lam = C12 / C44.
-// A grain's row holds sa P1 and sa P2 with sa^2 = |an|: 36 operations a stress, as the 21 entries of C
-// take, from 48 bytes instead of 84.  That is what a wavefront of several grains gathers per lane; the
-// explicit step went from 35.2 to 32.6 us at 128^3 (a grain is 8 sites wide), from 238 to 221 us for ten
-// 100^3 lattices (5 sites), and stays at 1.625 ms at 512^3 (32 sites).
+// the projectors P1, P2, P3 on the crystal axes, less a third of 1 each (so that they add up to 0),
+//     C e / C44 = lam tr(e) 1 + 2 e + an sum_a (P_a : e) P_a,   lam = C12 / C44 + an / 3.
+// A grain's row holds sa P1 and sa P2 with sa^2 = |an|: 33 operations a stress, against 36 with the 21
+// entries of C, from 48 bytes instead of 84.  That is what a wavefront of several grains gathers per lane;
+// the explicit step went from 35.2 to 32.6 us at 128^3 (a grain is 8 sites wide), from 238 to 221 us for ten
+// 100^3 lattices (5 sites), and stays at 1.625 ms at 512^3 (32 sites).  The third off each keeps the
+// entries, and with them the rounding, small: over random orientations and stresses the rows' rounding moves a
+// stress by 4.0e-8 (the 21 entries' by 4.4e-8, whole projectors' by 4.8e-8).
 struct CubicTab {
     const float* P;
-    float lam, sa, sgn;   // sgn: the sign of an
-    float C44;
+    float lam, lam_lo;    // the constant and what its rounding left
+    float sgn;            // of an
+    double C44;           // FP64: a rounded one shifts the macroscopic strain of every solve by up to 6e-8
 };
 
-// s = C e / C44 for row c; `on` is 1 (0, with lam and sa 0 too, gives 0 for a row of zeros).  The
+inline CubicTab cubic_tab(const hmc_ctx_s* c)
+{
+    const double an = (c->p.C11 - c->p.C12 - 2.0 * c->p.C44) / c->p.C44;
+    const double lam = c->p.C12 / c->p.C44 + an / 3.0;
+    return {c->d.Ptab, (float)lam, (float)(lam - (double)(float)lam), an < 0 ? -1.f : 1.f, c->p.C44};
+}
+
+// s = C e / C44 for row c; `on` is 1 (0, with lam and lam_lo 0 too, gives 0 for a row of zeros).  The
 // contractions are spelled out: every kernel and branch that forms a stress gives the same bits.
 template <class F>
-__device__ __forceinline__ void cubic_stress(const float c[kProjUsed], F lam, F sa, F sgn, F on, const F e[6], F s[6])
+__device__ __forceinline__ void cubic_stress(const float c[kProjUsed], F lam, F lam_lo, F sgn, F on, const F e[6],
+                                             F s[6])
 {
     auto dot = [&](int o) {
         F v = (F)c[o] * e[0];
@@ -65,10 +74,9 @@ __device__ __forceinline__ void cubic_stress(const float c[kProjUsed], F lam, F 
         return v;
     };
     const F tr = (e[0] + e[1]) + e[2];
-    const F p1 = dot(0), p2 = dot(6);
-    const F p3 = sgn * (fma(sa, tr, -p1) - p2);
-    const F h = fma(sa, p3, lam * tr);
-    const F q1 = fma(sgn, p1, -p3), q2 = fma(sgn, p2, -p3);
+    const F p1 = sgn * dot(0), p2 = sgn * dot(6);
+    const F h = fma(lam, tr, lam_lo * tr);
+    const F q1 = fma((F)2, p1, p2), q2 = fma((F)2, p2, p1);   // less the third axis' part, -(p1 + p2)
 #pragma unroll
     for (int I = 0; I < 6; ++I) {
         const F b = I < 3 ? fma(on + on, e[I], h) : on * e[I];
@@ -78,7 +86,7 @@ __device__ __forceinline__ void cubic_stress(const float c[kProjUsed], F lam, F 
 
 __device__ __forceinline__ void cubic_stress(const float c[kProjUsed], const CubicTab& T, const float e[6], float s[6])
 {
-    cubic_stress(c, T.lam, T.sa, T.sgn, 1.f, e, s);
+    cubic_stress(c, T.lam, T.lam_lo, T.sgn, 1.f, e, s);
 }
 
 __device__ __forceinline__ void cubic_row(const float* P, int q, float c[kProjUsed])
@@ -94,29 +102,32 @@ __device__ __forceinline__ void cubic_row(const float* P, int q, float c[kProjUs
     }
 }
 
+// Row g, the same in every active lane, through the scalar data cache.
+__device__ __forceinline__ void uniform_cubic_row(const float* P, int g, float c[kProjUsed])
+{
+    const UniformTab u = (UniformTab)(P + (int64_t)g * kProj);
+#pragma unroll
+    for (int i = 0; i < kProjUsed; ++i) c[i] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(u[i])));
+}
+
 // s = C_q e / C44.  A wavefront of one grain (with TWO: of one or two) takes its rows through the scalar
 // cache, which leaves the vector memory path (and its in-order wait counter) to the field data; in
 // any other each lane gathers its own 48 bytes.  Every way gives the same bits.
 template <bool TWO>
 __device__ __forceinline__ void cubic_grains(const CubicTab& T, int q, const float e[6], float s[6])
 {
-    auto row = [&](int g, float c[kProjUsed]) {   // g is the same in every active lane
-        const UniformTab u = (UniformTab)(T.P + (int64_t)g * kProj);
-#pragma unroll
-        for (int i = 0; i < kProjUsed; ++i) c[i] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(u[i])));
-    };
     const int q0 = __builtin_amdgcn_readfirstlane(q);
     const uint64_t other = __builtin_amdgcn_ballot_w64(q != q0);
     float c[kProjUsed];
     if (other == 0) {
-        row(q0, c);
+        uniform_cubic_row(T.P, q0, c);
         cubic_stress(c, T, e, s);
     } else {
         const int q1 = TWO ? __builtin_amdgcn_readlane(q, (int)__builtin_ctzll(other)) : 0;
         if (TWO && __builtin_amdgcn_ballot_w64(q != q0 && q != q1) == 0) {
-            row(q0, c);
+            uniform_cubic_row(T.P, q0, c);
             cubic_stress(c, T, e, s);
-            row(q1, c);
+            uniform_cubic_row(T.P, q1, c);
             if (q == q1) cubic_stress(c, T, e, s);
         } else {
             cubic_row(T.P, q, c);
@@ -131,6 +142,7 @@ __device__ __forceinline__ void cubic_grains(const CubicTab& T, int q, const flo
 // high corner is an own node, as 8 x 8 patches, one per wavefront (neighbouring voxels mostly
 // share a grain), then the low halo row and column.  kStepVox counts them for TY = 8.
 constexpr int kStepVox = (kTileX + 1) * (kTileY + 1);
+constexpr int kFlatThreads = 384;   // of the shallow steps: a thread a node column (340 of them)
 static_assert(kTileX == 32 && kTileY == 8, "voxel patches assume 32-wide tiles of 8, 16 or 32 rows");
 // For a 32 x TY tile (TY = 8, 16 or 32; 32 TY threads): wavefront w takes the 8 x 8 patch at x in
 // [8 (w % 4) + 1, 8 (w % 4) + 8], y in [8 (w / 4) + 1, 8 (w / 4) + 8].

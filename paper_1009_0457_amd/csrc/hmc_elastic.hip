@@ -148,7 +148,7 @@ __global__ __launch_bounds__(32 * TY, TY == 8 ? 4 : TY == 16 ? 2 : 1) void k_glo
     }
     if (lb == R.tile_first && threadIdx.x < kSumSlots) a.sums_clear[(int64_t)r * kSumSlots + threadIdx.x] = 0ull;
     float E[6];
-    const float alpha4 = 0.25f * R.alpha * C.C44, beta = R.beta;
+    const float alpha4 = (float)(0.25 * R.alpha * C.C44), beta = R.beta;
     const int t = threadIdx.x, lx = t % kTileX, ly = t / kTileX;
     const int nx = x0 + lx, ny = y0 + ly;
     const bool own = nx < K && ny < K;
@@ -306,7 +306,7 @@ __global__ __launch_bounds__(32 * TY, TY == 8 ? 4 : TY == 16 ? 2 : 1) void k_glo
     if (k < 6) {
         const unsigned copy = (unsigned)(lb - R.tile_first + (threadIdx.x >> 8)) & (kSumCopies - 1);
         atomicAdd(a.sums_out + (int64_t)r * kSumSlots + copy * 8 + k,
-                  (unsigned long long)llrint(tot * (kSumScale * (double)C.C44)));
+                  (unsigned long long)llrint(tot * (kSumScale * C.C44)));
     }
 }
 
@@ -316,7 +316,6 @@ __global__ __launch_bounds__(32 * TY, TY == 8 ? 4 : TY == 16 ? 2 : 1) void k_glo
 // and an own-node column), so the chain is arguments, fields and spins, the spins' stiffness rows, stores.
 // Voxels, sums and their order are those of the tiled step: the same bits.
 // Measured per step (kernel trace): 16^3 at depth 1 8.4 us tiled, 5.6 so; 64^3 at depth 2 12.0 and 8.4.
-constexpr int kFlatThreads = 384;
 template <int TZ>
 __global__ __launch_bounds__(kFlatThreads, 3) void k_global_step_flat(GlobArgs a)
 {
@@ -344,35 +343,36 @@ __global__ __launch_bounds__(kFlatThreads, 3) void k_global_step_flat(GlobArgs a
     const int t = threadIdx.x;
     const int KK = K * K;
 
-    // spins first: the stiffness rows wait for them
+    // Every thread loads, from a valid place where it has none of its own, so that the loads follow each
+    // other without a branch.  Spins first: the stiffness rows wait for them.
     int vx, vy;
     step_voxel_pos(t, vx, vy);
     const bool vox = t < kStepVox;
     const int vox_xy = wrap_tile(x0 - 1 + vx, K) + K * wrap_tile(y0 - 1 + vy, K);
     int sp[TZ + 1];
 #pragma unroll
-    for (int l = 0; l <= TZ; ++l) sp[l] = vox ? spins[vox_xy + (int64_t)KK * wrap_tile(z0 - 1 + l, K)] : 0;
+    for (int l = 0; l <= TZ; ++l) sp[l] = spins[vox_xy + (int64_t)KK * wrap_once(z0 - 1 + l, K)];
     const int ix = t % NX, iy = t / NX;
     const bool node = t < NX * NY;
     const int node_xy = wrap_tile(x0 - 1 + ix, K) + K * wrap_tile(y0 - 1 + iy, K);
     float un[TZ + 2][3];
 #pragma unroll
     for (int l = 0; l < TZ + 2; ++l) {
-        const int64_t n = node_xy + (int64_t)KK * wrap_tile(z0 - 1 + l, K);
+        const int64_t n = node_xy + (int64_t)KK * wrap_once(z0 - 1 + l, K);
 #pragma unroll
-        for (int j = 0; j < 3; ++j) un[l][j] = node ? uin[j * P + n] : 0.f;
+        for (int j = 0; j < 3; ++j) un[l][j] = uin[j * P + n];
     }
     const int lx = t % kTileX, ly = t / kTileX;
-    const int64_t own_n = x0 + lx + (int64_t)K * (y0 + ly) + (int64_t)KK * z0;
     const bool own = t < kTileX * kTileY && x0 + lx < K && y0 + ly < K;
+    const int64_t own_n = own ? x0 + lx + (int64_t)K * (y0 + ly) + (int64_t)KK * z0 : 0;
     float wz[TZ][3], uz[TZ][3];
 #pragma unroll
     for (int l = 0; l < TZ; ++l)
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-            const bool in = own && (TZ <= 2 || z0 + l < K);
-            wz[l][j] = in ? w[j * P + own_n + (int64_t)KK * l] : 0.f;
-            uz[l][j] = in ? uin[j * P + own_n + (int64_t)KK * l] : 0.f;
+            const int64_t i = j * P + own_n + (TZ <= 2 || z0 + l < K ? (int64_t)KK * l : 0);
+            wz[l][j] = w[i];
+            uz[l][j] = uin[i];
         }
     if (t >= kFlatThreads - 64 && t < kFlatThreads - 64 + 6) {   // the last wavefront has no voxels
         const int I = t - (kFlatThreads - 64);
@@ -426,10 +426,10 @@ __global__ __launch_bounds__(kFlatThreads, 3) void k_global_step_flat(GlobArgs a
         const double tot = (red[t][0] + red[t][1]) + (red[t][2] + red[t][3]);
         const unsigned copy = (unsigned)(lb - R.tile_first) & (kSumCopies - 1);
         atomicAdd(a.sums_out + (int64_t)r * kSumSlots + copy * 8 + t,
-                  (unsigned long long)llrint(tot * (kSumScale * (double)a.C.C44)));
+                  (unsigned long long)llrint(tot * (kSumScale * a.C.C44)));
     }
     if (own) {
-        const float alpha4 = 0.25f * R.alpha * a.C.C44, beta = R.beta;
+        const float alpha4 = (float)(0.25 * R.alpha * a.C.C44), beta = R.beta;
 #pragma unroll
         for (int l = 0; l < TZ; ++l) {
             if (TZ > 2 && z0 + l >= K) break;   // the last tile of an edge that TZ does not divide
@@ -461,7 +461,7 @@ __global__ void k_seq_fold(double* state, const double* st_last, const unsigned 
 struct FinalArgs {
     const int16_t* spins;
     const float* P;         // CubicTab's rows, and its constants in double
-    double lam, sa, sgn, C44;
+    double lam, sgn, C44;
     const float* u;
     float* sigma;       // may be null
     double* partials;
@@ -492,7 +492,7 @@ __global__ __launch_bounds__(256) void k_global_final(FinalArgs a)
         double e[6], s[6];
 #pragma unroll
         for (int I = 0; I < 6; ++I) e[I] = st[kE + I] + (double)g[I];
-        cubic_stress(c, a.lam, a.sa, a.sgn, 1.0, e, s);
+        cubic_stress(c, a.lam, 0.0, a.sgn, 1.0, e, s);
         double d = 0.0;
 #pragma unroll
         for (int I = 0; I < 6; ++I) {
@@ -621,13 +621,6 @@ __global__ __launch_bounds__(256) void k_texture(const int16_t* spins, const int
 
 // ---- launchers ----
 
-static CubicTab cubic_tab(const hmc_ctx_s* c)
-{
-    const double an = (c->p.C11 - c->p.C12 - 2.0 * c->p.C44) / c->p.C44;
-    return {c->d.Ptab, (float)(c->p.C12 / c->p.C44), (float)std::sqrt(std::fabs(an)), an < 0 ? -1.f : 1.f,
-            (float)c->p.C44};
-}
-
 hipError_t launch_reuss(hmc_ctx_s* c)
 {
     ReussArgs a;
@@ -734,8 +727,7 @@ hipError_t launch_global_final(hmc_ctx_s* c, bool write_sigma)
     a.spins = c->d.spins;
     const double an = (c->p.C11 - c->p.C12 - 2.0 * c->p.C44) / c->p.C44;
     a.P = c->d.Ptab;
-    a.lam = c->p.C12 / c->p.C44;
-    a.sa = std::sqrt(std::fabs(an));
+    a.lam = c->p.C12 / c->p.C44 + an / 3.0;
     a.sgn = an < 0 ? -1.0 : 1.0;
     a.C44 = c->p.C44;
     a.u = c->d.u[c->cur_u];

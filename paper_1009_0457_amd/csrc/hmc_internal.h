@@ -20,10 +20,12 @@ namespace hmc {
 // upper triangle row by row, padded to 24 floats (96 bytes).
 constexpr int kTab = 24;
 // The same stiffness from the projectors on two of a grain's crystal axes (a_i a_j in the Voigt
-// order xx, yy, zz, yz, xz, xy for the lab components a of the first and second axis), scaled as
-// CubicTab says: 12 floats, padded to 16 so that a row lies in one 64-byte line (rows of 48 bytes
+// order xx, yy, zz, yz, xz, xy for the lab components a of the first and second axis), less a third of 1 each
+// and scaled as CubicTab says: 12 floats, padded to 16 so that a row lies in one 64-byte line (rows of 48 bytes
 // cost the 512^3 explicit step 2.5 %: 1.666 against 1.625 ms).
 constexpr int kProj = 16, kProjUsed = 12;
+
+void axis_projectors(const double euler[3], double C11, double C12, double C44, double P[kProjUsed]);
 
 __host__ __device__ constexpr int sym_index(int i, int j)
 {

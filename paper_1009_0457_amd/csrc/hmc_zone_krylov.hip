@@ -91,7 +91,7 @@ __device__ __forceinline__ void corner_forces(float L0, float L1, float L2, floa
 struct KrylovArgs {
     ZoneArgs z;
     const float* Ptab;      // per-grain projectors (kProj)
-    float lam, sa, sgn;     // CubicTab's constants
+    float lam, lam_lo, sgn;  // CubicTab's constants
     float inv_scale;        // C44 / 16: the kernel's operator is 16 / C44 times A
 };
 
@@ -116,7 +116,7 @@ __global__ __launch_bounds__(64, 2) void k_zone_krylov(KrylovArgs ka)
     const bool vox = member && x < N;
     const bool centre_col = vox && x == H && y == H;
     const uint32_t count = *a.count;
-    const float on_vox = vox ? 1.f : 0.f, lam = vox ? ka.lam : 0.f, sa = vox ? ka.sa : 0.f;
+    const float on_vox = vox ? 1.f : 0.f, lam = vox ? ka.lam : 0.f, lam_lo = vox ? ka.lam_lo : 0.f;
 
     float* const ub = s_u + zs * TB;                              // this lane's trial block
     float* const nbk = s_n + S::PAD + zs * TB;
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(64, 2) void k_zone_krylov(KrylovArgs ka)
                 float Pp[3], Qp[3], Rp[3];
                 strains(p, [&](int kz, const float (&ev)[6]) {
                     float sv[6];
-                    cubic_stress<float>(Cv[kz], lam, sa, ka.sgn, on_vox, ev, sv);
+                    cubic_stress<float>(Cv[kz], lam, lam_lo, ka.sgn, on_vox, ev, sv);
                     const float Pn[3] = {sv[0], sv[5], sv[4]};
                     const float Qn[3] = {sv[5], sv[1], sv[3]};
                     const float Rn[3] = {sv[4], sv[3], sv[2]};
@@ -380,7 +380,7 @@ __global__ __launch_bounds__(64, 2) void k_zone_krylov(KrylovArgs ka)
             double quad = 0.0, lin = 0.0;
             strains(u, [&](int kz, const float (&ev)[6]) {
                 float sv[6];
-                cubic_stress<float>(Cv[kz], lam, sa, ka.sgn, on_vox, ev, sv);
+                cubic_stress<float>(Cv[kz], lam, lam_lo, ka.sgn, on_vox, ev, sv);
 #pragma unroll
                 for (int I = 0; I < 6; ++I) quad += (double)ev[I] * (double)sv[I];
                 if (kz == H && centre_col) {
@@ -501,9 +501,9 @@ void launch_zone_krylov(const hmc_params& p, int64_t max_list, const float* Ptab
     KrylovArgs a;
     a.z = za;
     a.Ptab = Ptab;
-    a.lam = (float)(p.C12 / p.C44);
-    const double an = (p.C11 - p.C12 - 2.0 * p.C44) / p.C44;
-    a.sa = (float)std::sqrt(std::fabs(an));
+    const double an = (p.C11 - p.C12 - 2.0 * p.C44) / p.C44, lam = p.C12 / p.C44 + an / 3.0;
+    a.lam = (float)lam;
+    a.lam_lo = (float)(lam - (double)a.lam);
     a.sgn = an < 0 ? -1.f : 1.f;
     a.inv_scale = (float)(p.C44 / 16.0);
     const int tw = p.zone_h == 2 ? KrylovShape<2>::TW : KrylovShape<3>::TW;

@@ -75,3 +75,26 @@ def test_shallow_step_in_a_batch_equals_alone():
             assert torch.equal(lat.get_stress(), b.get_stress(i)), (depth, K)
             lat.close()
         b.close()
+
+
+@pytest.mark.parametrize("K", [4, 6, 26, 34])
+def test_shallow_adjoint_step_matches_the_deep_one(K):
+    """The gradient by the depth-1 adjoint kernel against the tiled kernel at depth 8 (two to five blocks in
+    z above K = 8, the last one cut): the same sums in another order.  Each of the FP32 steps, forward and
+    backward, adds up to a unit in the last place (6e-8) to its field, so the two stay within 2e-6 of the
+    largest derivative over so few of them."""
+    m = voronoi_polycrystal(K, max(2, K ** 3 // 300), 95 + K)
+    grads = []
+    for depth in (1, 8):
+        print(f"[flat adjoint] K={K} depth={depth}", flush=True)
+        p = H.hmc_default_params(K, 26, 1)
+        p.refresh_tile_z = depth
+        lat = H.Lattice(p, m.Q)
+        lat.set_orientations(m.euler)
+        lat.set_spins(m.spins)
+        lat.set_load(SIG)
+        lat.elastic_forward(STEPS, 15)
+        grads.append([np.asarray(g, dtype=np.float64) for g in lat.elastic_backward(1.0)])
+        lat.close()
+    for flat, deep in zip(*grads):
+        assert np.abs(flat - deep).max() <= 2e-6 * np.abs(deep).max()
