@@ -408,8 +408,7 @@ hmc_status refresh(hmc_ctx c, int n_steps, bool cold)
 {
     TraceRange range(cold ? "hmc stress refresh (cold)" : "hmc stress refresh");
     if (c->p.material_points == 8) {
-        // nodes and velocities in place in the first displacement buffer, corner forces in
-        // the second
+        // the steps end in the first displacement buffer
         if (cold) {
             HMC_TRY(c, launch_fill_f32(c->d.u[0], 0.f, 3 * c->total_sites, c->stream), "refresh: clear u");
             HMC_TRY(c, launch_reuss(c), "refresh: uniform-stress start");
@@ -618,6 +617,7 @@ hmc_status build_context(const hmc_params* p, int n, const hmc_replica* r, void*
         R.node_blocks = (int)(nb > kMaxChunkBlocks ? kMaxChunkBlocks : nb);
         R.tile_first = tf;
         R.tile_z = balanced_depth(L.tile_z, R.K);
+        if (p->material_points == 8) mp8_tile(R.K, R.mp_tile);
         R.tile_y = L.tile_y;
         R.tile_blocks = tile_blocks_of(R.K, R.tile_z, R.tile_y);
         R.J = p->J;

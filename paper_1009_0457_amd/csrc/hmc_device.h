@@ -136,6 +136,25 @@ __device__ __forceinline__ void cubic_grains(const CubicTab& T, int q, const flo
     }
 }
 
+// (E, wE) of the step after the one that started from st_in and whose stress sums are in
+// sums (Sec. 5's average-stress control: r_E = Sigma - <sigma>, wE <- beta wE + alphaE r_E,
+// E <- E + wE), component I; sums == null: st_in unchanged.
+__device__ __forceinline__ void advance_E(const RepDev& R, int r, const double* st_in, int stride,
+                                          const unsigned long long* sums, int I, double& E_I, double& wE_I)
+{
+    E_I = st_in[(int64_t)r * stride + I];
+    wE_I = st_in[(int64_t)r * stride + 6 + I];
+    if (sums) {
+        const unsigned long long* sm = sums + (int64_t)r * kSumSlots + I;
+        long long tot = 0;
+#pragma unroll
+        for (int c = 0; c < kSumCopies; ++c) tot += (long long)sm[c * 8];
+        const double rE = R.Sigma[I] - (double)tot / (kSumScale * (double)R.n3);
+        wE_I = (double)R.glob_beta * wE_I + R.glob_alphaE * rE;
+        E_I += wE_I;
+    }
+}
+
 // Voxel positions of a 32 x TY node tile's layer (33 x (TY + 1) voxels, tile-relative; voxel
 // (ix, iy) has the tile's nodes ix, ix+1 and iy, iy+1 as corners, node 0 being the low halo)
 // in the order the 32 TY threads of a tiled step take them: first the 32 x TY voxels whose

@@ -56,26 +56,6 @@ __device__ __forceinline__ StepRep step_rep(const GlobArgs& a, int lb)
     return {r, R.K, R.tile_z, R.tile_first, R.glob_alpha, R.glob_beta, R.site_off, R.grain_off};
 }
 
-// (E, wE) of the step after the one that started from st_in and whose stress sums are in
-// sums (Sec. 5's average-stress control: r_E = Sigma - <sigma>, wE <- beta wE + alphaE r_E,
-// E <- E + wE), component I; sums == null: st_in unchanged.
-__device__ __forceinline__ void advance_E(const RepDev& R, int r, const double* st_in, int stride,
-                                          const unsigned long long* sums, int I, double& E_I, double& wE_I)
-{
-    E_I = st_in[(int64_t)r * stride + I];
-    wE_I = st_in[(int64_t)r * stride + 6 + I];
-    if (sums) {
-        const unsigned long long* sm = sums + (int64_t)r * kSumSlots + I;
-        long long tot = 0;
-#pragma unroll
-        for (int c = 0; c < kSumCopies; ++c) tot += (long long)sm[c * 8];
-        const double rE = R.Sigma[I] - (double)tot / (kSumScale * (double)R.n3);
-        wE_I = (double)R.glob_beta * wE_I + R.glob_alphaE * rE;
-        E_I += wE_I;
-    }
-}
-
-
 // Tiled explicit step.  A block owns a 32 x 8 tile of nodes in x, y and marches through
 // tile_z node layers in z, so each voxel stress is formed once per tile (1.3x with the halo
 // voxels) instead of once per corner node (8x).  The trilinear element's sums are factored

@@ -105,6 +105,7 @@ struct RepDev {
     int32_t elastic;                 // elastic term on for this replica (lambda != 0, load != 0)
     int32_t tile_z;                  // node layers per block of the tiled explicit step
     int32_t tile_y;                  // node rows per block of the forward explicit step (8 or 16)
+    int32_t mp_tile[3];              // nodes per block of the explicit step of 8 points per cell (mp8_tile)
     int64_t n3;
     int64_t site_off;                // into spins / sigma / u / w planes (sites)
     int64_t grain_off;               // into Ctab / Stab (grains)
@@ -273,6 +274,8 @@ hipError_t launch_global_final(hmc_ctx_s* c, bool write_sigma);
 // 2 x 2 x 2 material points per background cell (hmc_mp8.hip): n explicit steps, the final
 // point stresses and stored energy.
 hipError_t launch_mp8_steps(hmc_ctx_s* c, int n_steps);
+// A step's tile of nodes by the lattice edge alone (a replica's tiles are the same alone and in a batch).
+void mp8_tile(int K, int32_t tile[3]);
 // Grains of replica rep (hmc_grains.hip): per-site labels (the smallest site index of each
 // face-connected cluster of equal spins) and their number; host-synchronous.
 hipError_t launch_grain_labels(hmc_ctx_s* c, int rep, int32_t* labels, int64_t* n_grains, int* rounds);
