@@ -3,6 +3,7 @@
 // batch of replicas, and the order in which the kernels of a sweep are enqueued (optionally
 // captured once into HIP graphs and replayed).
 #include <cmath>
+#include <numeric>
 #include <cstdio>
 #include <cstring>
 #include <new>
@@ -209,7 +210,7 @@ Layout layout_of(const hmc_params* p, int n, const hmc_replica* r)
     L.thr = take((size_t)n * 64 * sizeof(uint64_t));
     L.tex = take((size_t)L.grains * sizeof(int32_t));
     L.hist = take(64 * sizeof(unsigned long long));
-    L.bonds = take(sizeof(unsigned long long));
+    L.bonds = take(kCountCopies * sizeof(unsigned long long));
     L.reps = take((size_t)n * sizeof(RepDev));
     L.pass_rep = take((size_t)L.pass_blocks * sizeof(int32_t));
     L.node_rep = take((size_t)L.node_blocks * sizeof(int32_t));
@@ -741,10 +742,10 @@ hmc_status energy_of(hmc_ctx c, int rep, int64_t* unlike, double* U)
 {
     if (!unlike || !U) return state_fail(c, HMC_EINVAL, "null output");
     if (!c->have_spins) return state_fail(c, HMC_ESTATE, "no spins set");
-    HMC_TRY(c, hipMemsetAsync(c->d.bonds, 0, sizeof(unsigned long long), c->stream), "energy");
+    HMC_TRY(c, hipMemsetAsync(c->d.bonds, 0, kCountCopies * sizeof(unsigned long long), c->stream), "energy");
     HMC_TRY(c, launch_unlike_bonds(c, rep), "energy");
-    unsigned long long slots = 0;
-    HMC_TRY(c, hipMemcpyAsync(&slots, c->d.bonds, sizeof slots, hipMemcpyDeviceToHost, c->stream), "energy");
+    unsigned long long slots[kCountCopies];
+    HMC_TRY(c, hipMemcpyAsync(slots, c->d.bonds, sizeof slots, hipMemcpyDeviceToHost, c->stream), "energy");
     double u = 0.0;
     if (c->elastic_buffers && c->have_state && c->have_orient) {
         if (c->p.material_points == 8)
@@ -756,7 +757,7 @@ hmc_status energy_of(hmc_ctx c, int rep, int64_t* unlike, double* U)
                 "energy");
     }
     HMC_TRY(c, hipStreamSynchronize(c->stream), "energy");
-    *unlike = (int64_t)(slots / 2);
+    *unlike = (int64_t)(std::accumulate(slots, slots + kCountCopies, 0ull) / 2);
     *U = u;
     return report_nonfinite(c);
 }
@@ -1392,8 +1393,7 @@ hmc_status hmc_grain_labels(hmc_ctx c, int32_t r, int32_t* labels_dev, int64_t* 
     c->err.clear();
     if (bad_rep(c, r) || !labels_dev || !n_grains) return state_fail(c, HMC_EINVAL, "bad replica or null argument");
     if (!c->have_spins) return state_fail(c, HMC_ESTATE, "no spins set");
-    int rounds = 0;
-    HMC_TRY(c, launch_grain_labels(c, r, labels_dev, n_grains, &rounds), "grain labels");
+    HMC_TRY(c, launch_grain_labels(c, r, labels_dev, n_grains), "grain labels");
     return HMC_OK;
 }
 

@@ -155,6 +155,19 @@ __device__ __forceinline__ void advance_E(const RepDev& R, int r, const double* 
     }
 }
 
+// The block's sum of n, times `times`, into one of the kCountCopies copies of a count (integers: order-free).
+__device__ __forceinline__ void block_count_to(unsigned long long* out, unsigned int n, unsigned int times)
+{
+    unsigned long long s = n;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    __shared__ unsigned long long part[4];
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        atomicAdd(out + (blockIdx.x & (kCountCopies - 1)), times * (part[0] + part[1] + part[2] + part[3]));
+}
+
 // Voxel positions of a 32 x TY node tile's layer (33 x (TY + 1) voxels, tile-relative; voxel
 // (ix, iy) has the tile's nodes ix, ix+1 and iy, iy+1 as corners, node 0 being the low halo)
 // in the order the 32 TY threads of a tiled step take them: first the 32 x TY voxels whose

@@ -139,7 +139,7 @@ constexpr double kSumScale = 67108864.0;       // 2^26
 constexpr int kSeqState = 16;
 
 // Counters (uint32): list counts per colour, error flag.
-enum CounterSlot { kListCount = 0, kErrFlag = 8, kLabelChanged = 9, kNonFinite = 10, kCounters = 16 };
+enum CounterSlot { kListCount = 0, kErrFlag = 8, kNonFinite = 10, kCounters = 16 };
 // Bits of counters[kNonFinite], raised by kernels that meet a non-finite value and reported
 // (then cleared) by the next call that synchronises the stream.
 enum NonFiniteBit { kNfGlobal = 1, kNfZone = 2, kNfInjected = 4 };
@@ -149,6 +149,9 @@ enum NonFiniteBit { kNfGlobal = 1, kNfZone = 2, kNfInjected = 4 };
 enum StatSlot { kStatReal = 0, kStatSolves = 1, kStatAccepted = 2, kStatScreened = 3, kStats = 8 };
 constexpr int kStatCopies = 64;
 __host__ __device__ constexpr int stat_copy(unsigned block) { return (int)(block & (kStatCopies - 1)) * kStats; }
+
+// Copies of a count over sites (unlike bonds, grains) that blocks pick by index and the host sums.
+constexpr int kCountCopies = 64;
 
 struct DeviceState {
     int16_t* spins = nullptr;        // sum of n3
@@ -169,7 +172,7 @@ struct DeviceState {
     uint64_t* thr = nullptr;         // n_rep x 64 integer Metropolis thresholds
     int32_t* tex_bin = nullptr;      // sum of Q
     unsigned long long* hist = nullptr;  // 64
-    unsigned long long* bonds = nullptr; // 1
+    unsigned long long* bonds = nullptr; // kCountCopies
     RepDev* reps = nullptr;          // n_rep
     int32_t* pass_rep = nullptr;     // block -> replica for colour passes
     int32_t* node_rep = nullptr;     // block -> replica for node kernels
@@ -278,7 +281,7 @@ hipError_t launch_mp8_steps(hmc_ctx_s* c, int n_steps);
 void mp8_tile(int K, int32_t tile[3]);
 // Grains of replica rep (hmc_grains.hip): per-site labels (the smallest site index of each
 // face-connected cluster of equal spins) and their number; host-synchronous.
-hipError_t launch_grain_labels(hmc_ctx_s* c, int rep, int32_t* labels, int64_t* n_grains, int* rounds);
+hipError_t launch_grain_labels(hmc_ctx_s* c, int rep, int32_t* labels, int64_t* n_grains);
 hipError_t launch_mp8_final(hmc_ctx_s* c, bool write_sigma);
 hipError_t launch_zero_wE(hmc_ctx_s* c);
 hipError_t launch_unlike_bonds(hmc_ctx_s* c, int rep);
