@@ -17,52 +17,48 @@ namespace hmc {
 // third words are multiplied by fixed odd constants, the high halves are mixed with the
 // other two words and the key, and the key is advanced by the golden-ratio Weyl steps.
 // ------------------------------------------------------------------------------------
-struct Philox4 {
-    uint32_t v[4];
-};
-
-// a ^ b ^ k in one instruction (gfx950's three-input bitwise op with truth table 0x96; the
-// compiler emits two XORs for it); k is the round key, uniform across the wavefront.
-__device__ __forceinline__ uint32_t xor3_key(uint32_t a, uint32_t b, uint32_t k)
+// a ^ b ^ k in one instruction (gfx950's three-input bitwise op with truth table 0x96).
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t k)
 {
-    uint32_t r;
-    asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0x96" : "=v"(r) : "v"(a), "v"(b), "s"(k));
-    return r;
+    return __builtin_amdgcn_bitop3_b32(a, b, k, 0x96);
 }
 
-__device__ __forceinline__ Philox4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
-                                                 uint32_t k0, uint32_t k1)
+// The first two words for the counter (c0, c1, 0, 0), c1 and the key the same in every lane: of the first two
+// rounds the compiler takes what c0 does not reach on the scalar unit.
+__device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t k0, uint32_t k1, uint32_t& v0,
+                                              uint32_t& v1)
 {
+    uint32_t c2 = 0, c3 = 0;
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
         // one 32 x 32 -> 64-bit product gives both halves (a single v_mad_u64_u32)
         const uint64_t pa = (uint64_t)0xD2511F53u * c0;
         const uint64_t pb = (uint64_t)0xCD9E8D57u * c2;
-        const uint32_t a = (uint32_t)pa, ah = (uint32_t)(pa >> 32);
-        const uint32_t b = (uint32_t)pb, bh = (uint32_t)(pb >> 32);
-        const uint32_t n0 = xor3_key(bh, c1, k0);
-        const uint32_t n2 = xor3_key(ah, c3, k1);
+        const uint32_t n0 = r < 2 ? (uint32_t)(pb >> 32) ^ (c1 ^ k0) : xor3((uint32_t)(pb >> 32), c1, k0);
+        const uint32_t n2 = r < 3 ? (uint32_t)(pa >> 32) ^ (c3 ^ k1) : xor3((uint32_t)(pa >> 32), c3, k1);
         c0 = n0;
-        c1 = b;
+        c1 = (uint32_t)pb;
         c2 = n2;
-        c3 = a;
+        c3 = (uint32_t)pa;
         k0 += 0x9E3779B9u;
         k1 += 0xBB67AE85u;
     }
-    Philox4 out;
-    out.v[0] = c0;
-    out.v[1] = c1;
-    out.v[2] = c2;
-    out.v[3] = c3;
-    return out;
+    v0 = c0;
+    v1 = c1;
 }
 
-__device__ __forceinline__ int wrapi(int a, int K) { return a < 0 ? a + K : (a >= K ? a - K : a); }
+// a in [-K, 2 K) into [0, K).
+__device__ __forceinline__ int wrapi(int a, int K)
+{
+    const uint32_t m = min((uint32_t)a, (uint32_t)(a + K));
+    return (int)min(m, m - (uint32_t)K);
+}
 
 struct PassArgs {
     int16_t* spins;                 // all replicas, end to end
     const RepDev* reps;
-    const int32_t* pass_rep;        // block -> replica
+    const int32_t* pass_rep;        // chunk -> replica
+    int single;                     // one replica: no table to read first
     const uint64_t* thr;            // per replica: 64 integer thresholds indexed by gb + M
     TrialEntry* list;
     uint32_t* list_count;
@@ -94,20 +90,8 @@ __device__ __forceinline__ double point_zone_energy(const float* __restrict__ So
     return d;
 }
 
-// 2-bit fields, for n = 0..26, of n % 3 (which = 0), (n / 3) % 3 (1) and n / 9 (2).
-constexpr uint64_t slot_field_table(int which)
-{
-    uint64_t t = 0;
-    for (int n = 0; n < 27; ++n) {
-        const int v = which == 0 ? n % 3 : which == 1 ? (n / 3) % 3 : n / 9;
-        t |= (uint64_t)v << (2 * n);
-    }
-    return t;
-}
-
 // Offset of neighbour slot k.  6: -x,+x,-y,+y,-z,+z.  26: (dz,dy,dx) lexicographic over
-// {-1,0,1}^3 without the centre (n = k or k + 1 past the centre; the digits of n in base 3
-// read from three constant bit tables, which a variable k turns into two shifts and masks).
+// {-1,0,1}^3 without the centre (n = k or k + 1 past the centre; n / 3 = 11 n >> 5 for n < 32).
 template <int M>
 __device__ __forceinline__ void slot_offset(int k, int& dx, int& dy, int& dz)
 {
@@ -116,11 +100,10 @@ __device__ __forceinline__ void slot_offset(int k, int& dx, int& dy, int& dz)
         dy = (k == 2) ? -1 : (k == 3 ? 1 : 0);
         dz = (k == 4) ? -1 : (k == 5 ? 1 : 0);
     } else {
-        constexpr uint64_t TX = slot_field_table(0), TY = slot_field_table(1), TZ = slot_field_table(2);
-        const int sh = 2 * (k + (k >= 13));
-        dx = (int)((TX >> sh) & 3u) - 1;
-        dy = (int)((TY >> sh) & 3u) - 1;
-        dz = (int)((TZ >> sh) & 3u) - 1;
+        const int n = k + (k >= 13), row = (11 * n) >> 5, layer = (11 * row) >> 5;
+        dx = n - 3 * row - 1;
+        dy = row - 3 * layer - 1;
+        dz = layer - 1;
     }
 }
 
@@ -179,45 +162,6 @@ __device__ __forceinline__ uint32_t site_of(int x, int y, int z, int K, int KK)
     return (uint32_t)x + __umul24((uint32_t)K, (uint32_t)y) + __umul24((uint32_t)KK, (uint32_t)z);
 }
 
-// Block-wide exclusive prefix sum of v (256 threads), with the block total.
-__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t& total)
-{
-    __shared__ uint32_t s_w[4];
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    uint32_t inc = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t n = __shfl_up(inc, off);
-        if (lane >= off) inc += n;
-    }
-    if (lane == 63) s_w[wid] = inc;
-    __syncthreads();
-    uint32_t before = 0;
-    for (int w = 0; w < wid; ++w) before += s_w[w];
-    total = s_w[0] + s_w[1] + s_w[2] + s_w[3];
-    __syncthreads();
-    return before + inc - v;
-}
-
-// Block-wide sums of two counts (256 threads), valid in thread 0.
-__device__ __forceinline__ void block_sum2(uint32_t& a, uint32_t& b)
-{
-    __shared__ uint32_t s_a[4], s_b[4];
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        a += __shfl_xor(a, off);
-        b += __shfl_xor(b, off);
-    }
-    if (lane == 0) {
-        s_a[wid] = a;
-        s_b[wid] = b;
-    }
-    __syncthreads();
-    a = s_a[0] + s_a[1] + s_a[2] + s_a[3];
-    b = s_b[0] + s_b[1] + s_b[2] + s_b[3];
-}
-
 // A chunk of kPassSites = 4 x 256 active sites belongs to one replica.  With SPT = 4 one
 // block covers a chunk and each thread takes four sites, 256 apart; with SPT = 1 four blocks
 // share a chunk, one site per thread (the same sites and draws, a quarter each).  Lattices
@@ -232,6 +176,11 @@ __device__ __forceinline__ void block_sum2(uint32_t& a, uint32_t& b)
 // thousands of blocks on large lattices, so the block appends its elastic trials with one
 // atomic on the list counter and adds its statistics to one of the spread counter copies.
 static_assert(kPassSites == 4 * 256, "a chunk is four sites per thread of a 256-thread block");
+// Bound by reading the whole lattice once a pass (the proposals reach nearly every line: 283 MB at 512^3, 4.2 TB/s) and
+// by VALU work (three quarters of the cycles: 117 operations a site, 35 of them Philox), on small lattices by its
+// chain of dependent reads.  Power-of-two sites by bit fields, what the first Philox rounds owe to the sweep
+// and the key on the scalar unit, counts from ballots instead of shuffles and the thresholds read with the spins
+// took a pass from 95.5 to 93.0 us at 512^3 (6 neighbours 216 to 190), 11.9 to 10.8 at 200^3, 6.15 to 5.5 at 128^3.
 // SCREEN: the lower-bound screen's FP64 path is compiled in only where it is used, since it
 // more than doubles the kernel's registers (126 against 48 VGPRs: 4 against 8 wavefronts per
 // SIMD, which hide the chain of dependent reads of every site).
@@ -245,7 +194,7 @@ __global__ __launch_bounds__(256) void k_potts_pass(PassArgs a)
     __shared__ uint32_t s_item[4][SPT * 64][3];      // per wavefront: coords, q_old | q_new << 16, r1
     const int lb = logical_block((int)blockIdx.x, (int)gridDim.x, a.order);   // neighbouring rows share an L2
     const int chunk = lb / SUB, sub = lb % SUB;
-    const int r = a.pass_rep[chunk];
+    const int r = a.single ? 0 : a.pass_rep[chunk];
     const RepDev R = a.reps[r];
     const uint32_t first =
         (uint32_t)(chunk - R.pass_first) * (uint32_t)kPassSites + (uint32_t)sub * 256u + threadIdx.x;
@@ -258,10 +207,16 @@ __global__ __launch_bounds__(256) void k_potts_pass(PassArgs a)
     const uint32_t sweep = (uint32_t)(*a.sweep);
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const unsigned long long below = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
-    uint32_t n_real = 0, n_other = 0, n_wave = 0;
+    uint32_t n_wave = 0;
     const uint32_t Kh = (uint32_t)R.Kh, NJ = (M == 26) ? Kh : (uint32_t)K;
-    const uint32_t di = 256u % Kh, dr = 256u / Kh;
-    ActiveWalk walk = walk_start(first, Kh, NJ);
+    const int lg = 31 - __builtin_clz((unsigned)K);   // NP2: K = 2^lg
+    const uint32_t di = NP2 ? 0u : 256u % Kh, dr = NP2 ? 0u : 256u / Kh;
+    ActiveWalk walk{0u, 0u, 0u};
+    if (!NP2) walk = walk_start(first, Kh, NJ);
+    // the zero-load decisions' thresholds, read with the spins and put down with the lists
+    __shared__ uint64_t s_thr[64];
+    uint64_t thr = 0;
+    if (!elastic && threadIdx.x < 64) thr = a.thr[(int64_t)r * 64 + threadIdx.x];
 
     // ---- phase 1: draws, proposals; real flips to the wavefront's list ----
     // In three stages, so that all of a thread's spin reads are in flight together: the sites
@@ -271,21 +226,26 @@ __global__ __launch_bounds__(256) void k_potts_pass(PassArgs a)
     bool ok[SPT];
 #pragma unroll
     for (int it = 0; it < SPT; ++it) {
-        if (it > 0) walk_advance(walk, Kh, NJ, di, dr);
-        ok[it] = first + (uint32_t)it * 256u < n_active;
+        const uint32_t t = first + (uint32_t)it * 256u;
+        ok[it] = t < n_active;
+        if (NP2)   // the class's (i, j, k) are bit fields of the index
+            walk = {t & (Kh - 1), (t >> (lg - 1)) & (NJ - 1), t >> (M == 26 ? 2 * lg - 2 : 2 * lg - 1)};
+        else if (it > 0)
+            walk_advance(walk, Kh, NJ, di, dr);
         int x, y, z;
         walk_site<M>(walk, a.colour, x, y, z);
-        site[it] = site_of(x, y, z, K, KK);
+        site[it] = NP2 ? (uint32_t)x | ((uint32_t)y << lg) | ((uint32_t)z << (2 * lg)) : site_of(x, y, z, K, KK);
         packed[it] = (uint32_t)x | ((uint32_t)y << 10) | ((uint32_t)z << 20);
-        const Philox4 rn = philox4x32_10(site[it], sweep, 0u, 0u, R.key0, R.key1);
-        r0[it] = rn.v[0];
-        r1[it] = rn.v[1];
+        philox4x32_10(site[it], sweep, R.key0, R.key1, r0[it], r1[it]);
         nbr[it] = site[it];
         if (nbr_prop) {
-            const int k = (int)__umulhi(rn.v[0], (uint32_t)M);
+            const int k = (int)__umulhi(r0[it], (uint32_t)M);
             int dx, dy, dz;
             slot_offset<M>(k, dx, dy, dz);
-            if (pow2)   // uniform branch: a power-of-two edge wraps by a mask
+            if (NP2)
+                nbr[it] = (uint32_t)((x + dx) & Km) | ((uint32_t)((y + dy) & Km) << lg) |
+                          ((uint32_t)((z + dz) & Km) << (2 * lg));
+            else if (pow2)   // uniform branch: a power-of-two edge wraps by a mask
                 nbr[it] = site_of((x + dx) & Km, (y + dy) & Km, (z + dz) & Km, K, KK);
             else
                 nbr[it] = site_of(wrapi(x + dx, K), wrapi(y + dy, K), wrapi(z + dz, K), K, KK);
@@ -333,22 +293,21 @@ __global__ __launch_bounds__(256) void k_potts_pass(PassArgs a)
             s_item[wid][j][2] = r1[it];
         }
         n_wave += (uint32_t)__popcll(m);
-        n_real += real ? 1u : 0u;
     }
     __shared__ uint32_t s_nw[4];
     if (lane == 0) s_nw[wid] = n_wave;
+    if (!elastic && threadIdx.x < 64) s_thr[threadIdx.x] = thr;
     __syncthreads();
     // the four wavefronts' lists, read as one list of the block's real flips
     const uint32_t c0 = s_nw[0], c1 = c0 + s_nw[1], c2 = c1 + s_nw[2], n_block = c2 + s_nw[3];
 
     // ---- phase 2: the block's real flips, 256 at a time (wavefronts past the end skip it) ----
     TrialEntry ent[SPT];
-    bool solve[SPT];
-    uint32_t n_solve = 0;
+    bool solve[SPT], other[SPT];   // to the list; screened or (zero load) accepted
 #pragma unroll
     for (int it = 0; it < SPT; ++it) {
         const uint32_t j = (uint32_t)(it * 256) + threadIdx.x;
-        solve[it] = false;
+        solve[it] = other[it] = false;
         if (j < n_block) {
             const int wv = (j >= c0) + (j >= c1) + (j >= c2);
             const uint32_t jj = j - (wv == 0 ? 0u : wv == 1 ? c0 : wv == 2 ? c1 : c2);
@@ -373,12 +332,13 @@ __global__ __launch_bounds__(256) void k_potts_pass(PassArgs a)
             for (int k = 0; k < M; ++k) {
                 int dx, dy, dz;
                 slot_offset<M>(k, dx, dy, dz);
-                const int qn = *reinterpret_cast<const int16_t*>(sb + (xs[dx + 1] + ys[dy + 1] + zs[dz + 1]));
-                gb += (qn == q_old) - (qn == q_new);
+                const uint32_t qn =
+                    *reinterpret_cast<const unsigned short*>(sb + (xs[dx + 1] + ys[dy + 1] + zs[dz + 1]));
+                gb += (int)(qn != (uint32_t)q_new) - (int)(qn != (uint32_t)q_old);
             }
             bool accepted = false, screened = false;
             if (!elastic) {
-                accepted = (uint64_t)r1 < a.thr[(int64_t)r * 64 + gb + M];
+                accepted = (uint64_t)r1 < s_thr[gb + M];
             } else if (SCREEN && r1 != 0u) {
                 // reject without a solve when even the lowest possible zone energy loses:
                 // dE >= J gb + lambda dPi_0 > max(0, E*(r1)) + margin
@@ -416,30 +376,45 @@ __global__ __launch_bounds__(256) void k_potts_pass(PassArgs a)
             ent[it].qr = (uint32_t)q_new | ((uint32_t)r << 16);
             ent[it].gb = gb;
             ent[it].r1 = r1;
-            n_solve += solve[it] ? 1u : 0u;
-            n_other += (elastic ? screened : accepted) ? 1u : 0u;
+            other[it] = elastic ? screened : accepted;
         }
     }
     // block-collective tail, reached by every thread (`elastic` is uniform over the block: a
-    // block belongs to one replica; at zero load nothing enters the list)
-    uint32_t off = 0;
-    __shared__ uint32_t s_base;
-    if (elastic) {
-        uint32_t total = 0;
-        off = block_exclusive_scan(n_solve, total);
-        if (threadIdx.x == 0) s_base = total ? atomicAdd(a.list_count, total) : 0u;
+    // block belongs to one replica; at zero load nothing enters the list).  Counts come from ballots; the
+    // block's real flips are n_block.
+    __shared__ uint32_t s_other[4], s_solve[4], s_base;
+    uint32_t n_other = 0, n_solve = 0, slot[SPT];
+#pragma unroll
+    for (int it = 0; it < SPT; ++it) {
+        n_other += (uint32_t)__popcll(__ballot(other[it]));
+        if (elastic) {
+            const unsigned long long m = __ballot(solve[it]);
+            slot[it] = n_solve + (uint32_t)__popcll(m & below);
+            n_solve += (uint32_t)__popcll(m);
+        }
     }
-    block_sum2(n_real, n_other);   // (its barrier also publishes s_base)
+    if (lane == 0) {
+        s_other[wid] = n_other;
+        s_solve[wid] = n_solve;
+    }
+    __syncthreads();
     if (threadIdx.x == 0) {
+        if (elastic) {
+            const uint32_t total = s_solve[0] + s_solve[1] + s_solve[2] + s_solve[3];
+            s_base = total ? atomicAdd(a.list_count, total) : 0u;
+        }
         unsigned long long* st = a.stats + stat_copy(blockIdx.x);
-        if (n_real) atomicAdd(&st[kStatReal], (unsigned long long)n_real);
-        if (n_other) atomicAdd(&st[elastic ? kStatScreened : kStatAccepted], (unsigned long long)n_other);
+        const uint32_t others = s_other[0] + s_other[1] + s_other[2] + s_other[3];
+        if (n_block) atomicAdd(&st[kStatReal], (unsigned long long)n_block);
+        if (others) atomicAdd(&st[elastic ? kStatScreened : kStatAccepted], (unsigned long long)others);
     }
     if (elastic) {
-        off += s_base;
+        __syncthreads();
+        uint32_t off = s_base;
+        for (int w = 0; w < wid; ++w) off += s_solve[w];
 #pragma unroll
         for (int it = 0; it < SPT; ++it)
-            if (solve[it]) a.list[off++] = ent[it];
+            if (solve[it]) a.list[off + slot[it]] = ent[it];
     }
 }
 
@@ -560,6 +535,7 @@ hipError_t launch_potts_pass(hmc_ctx_s* c, int colour, hmc_trial_record* rec)
     a.spins = c->d.spins;
     a.reps = c->d.reps;
     a.pass_rep = c->d.pass_rep;
+    a.single = c->n_rep == 1;
     a.thr = c->d.thr;
     a.list = c->d.list;
     a.list_count = c->d.counters + kListCount + colour;
