@@ -215,7 +215,7 @@ Layout layout_of(const hmc_params* p, int n, const hmc_replica* r)
     L.pass_rep = take((size_t)L.pass_blocks * sizeof(int32_t));
     L.node_rep = take((size_t)L.node_blocks * sizeof(int32_t));
     L.tile_rep = take((size_t)L.tile_blocks * sizeof(int32_t));
-    L.sweep = take(sizeof(int64_t));
+    L.sweep = take(2 * sizeof(int64_t));
     L.total = o;
     return L;
 }
@@ -468,6 +468,11 @@ hmc_status enqueue_sweep(hmc_ctx c, bool with_refresh)
     if (with_refresh) {
         hmc_status st = refresh(c, c->p.refresh_steps, false);
         if (st != HMC_OK) return st;
+    }
+    if (pairs_colours(c)) {   // the last pair advances the sweep index
+        for (int pair = 0; pair < 4; ++pair) HMC_TRY(c, launch_potts_pair(c, pair), "sweep: two colours");
+        c->host_site_trials += c->total_sites;
+        return HMC_OK;
     }
     for (int col = 0; col < c->colours; ++col) {
         hmc_status st = run_pass(c, col, nullptr);

@@ -44,6 +44,7 @@ constexpr int kMaxReplicas = 4096;
 constexpr int kSiteBlock = 256;        // nodes per block of node-parallel kernels
 constexpr int kPassSites = 1024;       // active sites per chunk of a colour pass (one replica's)
 constexpr int kPassSplitBelow = 1024;  // passes with fewer chunks run one site per thread
+constexpr int64_t kPairBelow = 1 << 20;   // zero-load sweeps with fewer trials a colour take two colours a launch
 constexpr int kMaxChunkBlocks = 8192;  // blocks per replica of node-parallel reductions
 constexpr int kTileX = 32, kTileY = 8;   // node tile of the explicit step in x, y
 constexpr int kTileZMax = 32;            // deepest tile in z (node layers per block)
@@ -177,7 +178,7 @@ struct DeviceState {
     int32_t* pass_rep = nullptr;     // block -> replica for colour passes
     int32_t* node_rep = nullptr;     // block -> replica for node kernels
     int32_t* tile_rep = nullptr;     // block -> replica for the tiled explicit step
-    int64_t* sweep = nullptr;        // device copy of the sweep index (Philox counter)
+    int64_t* sweep = nullptr;        // device copy of the sweep index (Philox counter); a second slot for k_potts_pair
 };
 
 }  // namespace hmc
@@ -261,6 +262,10 @@ hipError_t launch_convert_spins(const int32_t* in, int16_t* out, int64_t n, int3
 hipError_t launch_export_spins(const int16_t* in, int32_t* out, int64_t n, hipStream_t s);
 // Raises `bit` in *flag if any of the n floats at p is not finite.
 hipError_t launch_check_finite(const float* p, int64_t n, uint32_t* flag, uint32_t bit, hipStream_t s);
+// Small zero-load lattices of one edge, 26 neighbours: a sweep is four launches of two colours each, which also
+// advance the sweep index.
+bool pairs_colours(const hmc_ctx_s* c);
+hipError_t launch_potts_pair(hmc_ctx_s* c, int pair);
 hipError_t launch_potts_pass(hmc_ctx_s* c, int colour, hmc_trial_record* rec);
 hipError_t launch_zone_pass(hmc_ctx_s* c, int colour, hmc_trial_record* rec);
 hipError_t launch_apply_pass(hmc_ctx_s* c, int colour);

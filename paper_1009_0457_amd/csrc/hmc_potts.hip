@@ -59,12 +59,13 @@ struct PassArgs {
     const RepDev* reps;
     const int32_t* pass_rep;        // chunk -> replica
     int single;                     // one replica: no table to read first
+    int rep_blocks;                 // k_potts_pair: blocks of each replica
     const uint64_t* thr;            // per replica: 64 integer thresholds indexed by gb + M
     TrialEntry* list;
     uint32_t* list_count;
     hmc_trial_record* rec;          // indexed by site_off + site, or null
     unsigned long long* stats;
-    const int64_t* sweep;           // Philox counter word 1 (low 32 bits)
+    int64_t* sweep;                 // Philox counter word 1 (low 32 bits); the second slot is k_potts_pair's
     const float* Stab;              // compliance tables (lower-bound screen)
     const float* sigma;             // stress planes of `plane` floats (lower-bound screen)
     int64_t plane;
@@ -162,6 +163,43 @@ __device__ __forceinline__ uint32_t site_of(int x, int y, int z, int K, int KK)
     return (uint32_t)x + __umul24((uint32_t)K, (uint32_t)y) + __umul24((uint32_t)KK, (uint32_t)z);
 }
 
+// Site (x + dx, y + dy, z + dz) of the periodic lattice; POW2: K = 2^lg.
+template <bool POW2>
+__device__ __forceinline__ uint32_t neighbour_site(int x, int y, int z, int K, int KK, int lg)
+{
+    if (POW2) {
+        const int Km = K - 1;
+        return (uint32_t)(x & Km) | ((uint32_t)(y & Km) << lg) | ((uint32_t)(z & Km) << (2 * lg));
+    }
+    return site_of(wrapi(x, K), wrapi(y, K), wrapi(z, K), K, KK);
+}
+
+// Change of the unlike neighbours of (x, y, z) from state q_old to q_new.
+template <int M>
+__device__ __forceinline__ int unlike_change(const int16_t* spins, int x, int y, int z, int K, int KK, int q_old,
+                                             int q_new)
+{
+    // byte offsets of the three x, y and z planes around the site (2 bytes per spin;
+    // 2 K^3 <= 2^31 for K <= 1024): each neighbour is one add and a load off the
+    // replica's spin base
+    const uint32_t K2 = 2u * (uint32_t)K, KK2 = 2u * (uint32_t)KK;
+    const uint32_t xs[3] = {2u * (uint32_t)wrapi(x - 1, K), 2u * (uint32_t)x, 2u * (uint32_t)wrapi(x + 1, K)};
+    const uint32_t ys[3] = {(uint32_t)__umul24((uint32_t)wrapi(y - 1, K), K2), (uint32_t)__umul24((uint32_t)y, K2),
+                            (uint32_t)__umul24((uint32_t)wrapi(y + 1, K), K2)};
+    const uint32_t zs[3] = {(uint32_t)__umul24((uint32_t)wrapi(z - 1, K), KK2), (uint32_t)__umul24((uint32_t)z, KK2),
+                            (uint32_t)__umul24((uint32_t)wrapi(z + 1, K), KK2)};
+    const char* sb = reinterpret_cast<const char*>(spins);
+    int gb = 0;
+#pragma unroll
+    for (int k = 0; k < M; ++k) {
+        int dx, dy, dz;
+        slot_offset<M>(k, dx, dy, dz);
+        const uint32_t qn = *reinterpret_cast<const unsigned short*>(sb + (xs[dx + 1] + ys[dy + 1] + zs[dz + 1]));
+        gb += (int)(qn != (uint32_t)q_new) - (int)(qn != (uint32_t)q_old);
+    }
+    return gb;
+}
+
 // A chunk of kPassSites = 4 x 256 active sites belongs to one replica.  With SPT = 4 one
 // block covers a chunk and each thread takes four sites, 256 apart; with SPT = 1 four blocks
 // share a chunk, one site per thread (the same sites and draws, a quarter each).  Lattices
@@ -243,12 +281,11 @@ __global__ __launch_bounds__(256) void k_potts_pass(PassArgs a)
             int dx, dy, dz;
             slot_offset<M>(k, dx, dy, dz);
             if (NP2)
-                nbr[it] = (uint32_t)((x + dx) & Km) | ((uint32_t)((y + dy) & Km) << lg) |
-                          ((uint32_t)((z + dz) & Km) << (2 * lg));
+                nbr[it] = neighbour_site<true>(x + dx, y + dy, z + dz, K, KK, lg);
             else if (pow2)   // uniform branch: a power-of-two edge wraps by a mask
                 nbr[it] = site_of((x + dx) & Km, (y + dy) & Km, (z + dz) & Km, K, KK);
             else
-                nbr[it] = site_of(wrapi(x + dx, K), wrapi(y + dy, K), wrapi(z + dz, K), K, KK);
+                nbr[it] = neighbour_site<false>(x + dx, y + dy, z + dz, K, KK, lg);
         }
     }
     int q_old[SPT], q_nb[SPT];
@@ -315,27 +352,7 @@ __global__ __launch_bounds__(256) void k_potts_pass(PassArgs a)
             const int x = (int)(packed & 1023u), y = (int)((packed >> 10) & 1023u), z = (int)(packed >> 20);
             const int q_old = (int)(qq & 0xffffu), q_new = (int)(qq >> 16);
             const uint32_t site = site_of(x, y, z, K, KK);
-            // byte offsets of the three x, y and z planes around the site (2 bytes per spin;
-            // 2 K^3 <= 2^31 for K <= 1024): each neighbour is one add and a load off the
-            // replica's spin base
-            const uint32_t K2 = 2u * (uint32_t)K, KK2 = 2u * (uint32_t)KK;
-            const uint32_t xs[3] = {2u * (uint32_t)wrapi(x - 1, K), 2u * (uint32_t)x, 2u * (uint32_t)wrapi(x + 1, K)};
-            const uint32_t ys[3] = {(uint32_t)__umul24((uint32_t)wrapi(y - 1, K), K2),
-                                    (uint32_t)__umul24((uint32_t)y, K2),
-                                    (uint32_t)__umul24((uint32_t)wrapi(y + 1, K), K2)};
-            const uint32_t zs[3] = {(uint32_t)__umul24((uint32_t)wrapi(z - 1, K), KK2),
-                                    (uint32_t)__umul24((uint32_t)z, KK2),
-                                    (uint32_t)__umul24((uint32_t)wrapi(z + 1, K), KK2)};
-            const char* sb = reinterpret_cast<const char*>(spins);
-            int gb = 0;
-#pragma unroll
-            for (int k = 0; k < M; ++k) {
-                int dx, dy, dz;
-                slot_offset<M>(k, dx, dy, dz);
-                const uint32_t qn =
-                    *reinterpret_cast<const unsigned short*>(sb + (xs[dx + 1] + ys[dy + 1] + zs[dz + 1]));
-                gb += (int)(qn != (uint32_t)q_new) - (int)(qn != (uint32_t)q_old);
-            }
+            const int gb = unlike_change<M>(spins, x, y, z, K, KK, q_old, q_new);
             bool accepted = false, screened = false;
             if (!elastic) {
                 accepted = (uint64_t)r1 < s_thr[gb + M];
@@ -415,6 +432,122 @@ __global__ __launch_bounds__(256) void k_potts_pass(PassArgs a)
 #pragma unroll
         for (int it = 0; it < SPT; ++it)
             if (solve[it]) a.list[off + slot[it]] = ent[it];
+    }
+}
+
+// Two colours in one launch, for lattices of one edge at zero load with 26 neighbours: the colours 2p and 2p + 1 share
+// their rows (the y and z parities of p) and alternate along x, so the only sites of one among the neighbours
+// of the other lie in the same row, and every other neighbour belongs to no row of the launch.  A block owns whole
+// rows, a thread a site of each colour, and takes the first colour, a barrier, and the second: the same trials on the
+// same spins as two launches.  The draws and reads of both go out first; a second-colour site that proposes its
+// row neighbour's state reads it again after the barrier.  The last pair also advances the sweep index: the
+// first (p = 0) copies it to a second slot, which the others read, so that no block reads the slot that is
+// written.  A sweep is four launches instead of nine, for lattices whose launch is a chain of waits: a colour of 128^3
+// 5.4 -> 4.2 us, of 64^3 4.6 -> 2.8, of ten 60^3 6.3 -> 4.1, of 200^3 10.9 -> 10.75.  Large ones are better off with four
+// sites a thread and a launch a colour (512^3 92.7 us; so 110, and 95 with four sites a thread here).
+template <bool NP2>
+__global__ __launch_bounds__(256) void k_potts_pair(PassArgs a)
+{
+    constexpr int M = 26;
+    __shared__ uint32_t s_item[4][64][3];   // per wavefront: coords, q_old | q_new << 16, r1
+    __shared__ uint32_t s_nw[4], s_acc[4];
+    __shared__ uint64_t s_thr[64];
+    const int lb = logical_block((int)blockIdx.x, (int)gridDim.x, a.order);
+    const int r = a.single ? 0 : lb / a.rep_blocks, block = lb - r * a.rep_blocks;
+    const RepDev R = a.reps[r];
+    const int K = R.K, KK = K * K, py = a.colour & 1, pz = a.colour >> 1;
+    const uint32_t Kh = (uint32_t)R.Kh, rows = 256u / Kh, inv = 0xffffffffu / Kh + 1u;   // n / Kh = n inv >> 32
+    const int lg = 31 - __builtin_clz((unsigned)K);   // NP2: K = 2^lg
+    const bool nbr_prop = NP2 || R.proposal == 0;
+    int16_t* spins = a.spins + R.site_off;
+    const int64_t sweep64 = a.sweep[a.colour == 0 ? 0 : 1];
+    const uint32_t sweep = (uint32_t)sweep64;
+    if (lb == 0 && threadIdx.x == 0) {
+        if (a.colour == 0) a.sweep[1] = sweep64;
+        if (a.colour == 3) a.sweep[0] = sweep64 + 1;
+    }
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const unsigned long long below = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
+    uint64_t thr = 0;
+    if (threadIdx.x < 64) thr = a.thr[(int64_t)r * 64 + threadIdx.x];
+
+    const uint32_t row = NP2 ? threadIdx.x >> (lg - 1) : __umulhi(threadIdx.x, inv), i = threadIdx.x - row * Kh;
+    const uint32_t rr = (uint32_t)block * rows + row, k = NP2 ? rr >> (lg - 1) : __umulhi(rr, inv), j = rr - k * Kh;
+    const bool ok = row < rows && rr < Kh * Kh;
+    const int y = 2 * (int)j + py, z = 2 * (int)k + pz;
+    auto spin = [&](uint32_t v) {
+        return (int)*reinterpret_cast<const int16_t*>(reinterpret_cast<const char*>(spins) + 2u * v);
+    };
+    uint32_t nbr[2], r0[2], r1[2];
+    int q_old[2] = {0, 0}, q_nb[2] = {0, 0};
+    bool again = false;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const int x = 2 * (int)i + c;
+        const uint32_t site = NP2 ? neighbour_site<true>(x, y, z, K, KK, lg) : site_of(x, y, z, K, KK);
+        philox4x32_10(site, sweep, R.key0, R.key1, r0[c], r1[c]);
+        nbr[c] = site;
+        if (nbr_prop) {
+            const int slot = (int)__umulhi(r0[c], (uint32_t)M);
+            int dx, dy, dz;
+            slot_offset<M>(slot, dx, dy, dz);
+            nbr[c] = neighbour_site<NP2>(x + dx, y + dy, z + dz, K, KK, lg);
+            if (c == 1) again = slot == 12 || slot == 13;   // x - 1 or x + 1
+        }
+        if (ok) {
+            q_old[c] = spin(site);
+            q_nb[c] = spin(nbr[c]);
+        }
+    }
+    uint32_t n_real = 0, n_acc = 0;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        bool real = false;
+        uint32_t qq = 0;
+        if (ok) {
+            if (c == 1 && again) q_nb[1] = spin(nbr[1]);
+            int q_new = q_nb[c];
+            if (!nbr_prop) {
+                const uint32_t step = __umulhi(r0[c], (uint32_t)(R.Q - 1));
+                q_new = (int)(((uint32_t)q_old[c] + 1u + step) % (uint32_t)R.Q);
+            }
+            real = q_new != q_old[c];
+            qq = (uint32_t)q_old[c] | ((uint32_t)q_new << 16);
+        }
+        const unsigned long long m = __ballot(real);
+        if (real) {
+            const uint32_t at = (uint32_t)__popcll(m & below);
+            s_item[wid][at][0] = (uint32_t)(2 * (int)i + c) | ((uint32_t)y << 10) | ((uint32_t)z << 20);
+            s_item[wid][at][1] = qq;
+            s_item[wid][at][2] = r1[c];
+        }
+        if (lane == 0) s_nw[wid] = (uint32_t)__popcll(m);
+        if (c == 0 && threadIdx.x < 64) s_thr[threadIdx.x] = thr;
+        __syncthreads();
+        // the four wavefronts' lists, read as one list of the block's real flips
+        const uint32_t c0 = s_nw[0], c1 = c0 + s_nw[1], c2 = c1 + s_nw[2], n_block = c2 + s_nw[3];
+        n_real += n_block;
+        bool accepted = false;
+        if (threadIdx.x < n_block) {
+            const uint32_t t = threadIdx.x;
+            const int wv = (t >= c0) + (t >= c1) + (t >= c2);
+            const uint32_t at = t - (wv == 0 ? 0u : wv == 1 ? c0 : wv == 2 ? c1 : c2);
+            const uint32_t p = s_item[wv][at][0], qs = s_item[wv][at][1];
+            const int sx = (int)(p & 1023u), sy = (int)((p >> 10) & 1023u), sz = (int)(p >> 20), q_new = (int)(qs >> 16);
+            const int gb = unlike_change<M>(spins, sx, sy, sz, K, KK, (int)(qs & 0xffffu), q_new);
+            accepted = (uint64_t)s_item[wv][at][2] < s_thr[gb + M];
+            if (accepted) spins[site_of(sx, sy, sz, K, KK)] = (int16_t)q_new;
+        }
+        n_acc += (uint32_t)__popcll(__ballot(accepted));
+        if (c == 0) __syncthreads();   // the first colour's spins are written, and the lists are free
+    }
+    if (lane == 0) s_acc[wid] = n_acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long* st = a.stats + stat_copy(blockIdx.x);
+        const uint32_t acc = s_acc[0] + s_acc[1] + s_acc[2] + s_acc[3];
+        if (n_real) atomicAdd(&st[kStatReal], (unsigned long long)n_real);
+        if (acc) atomicAdd(&st[kStatAccepted], (unsigned long long)acc);
     }
 }
 
@@ -529,13 +662,12 @@ hipError_t launch_add_i64(int64_t* p, int64_t v, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_potts_pass(hmc_ctx_s* c, int colour, hmc_trial_record* rec)
+static PassArgs pass_args(const hmc_ctx_s* c, int colour, hmc_trial_record* rec)
 {
     PassArgs a;
     a.spins = c->d.spins;
     a.reps = c->d.reps;
     a.pass_rep = c->d.pass_rep;
-    a.single = c->n_rep == 1;
     a.thr = c->d.thr;
     a.list = c->d.list;
     a.list_count = c->d.counters + kListCount + colour;
@@ -548,13 +680,54 @@ hipError_t launch_potts_pass(hmc_ctx_s* c, int colour, hmc_trial_record* rec)
     a.colour = colour;
     a.order = c->block_order;
     a.screen = (c->p.zone_screen != 0 && c->d.sigma != nullptr) ? 1 : 0;
+    a.single = c->n_rep == 1;
+    a.rep_blocks = 0;
+    return a;
+}
+
+// Every replica proposes a neighbour's state and has a power-of-two edge.
+static bool pow2_neighbours(const hmc_ctx_s* c)
+{
+    bool np2 = true;
+    for (const RepDev& R : c->reps) np2 = np2 && R.proposal == 0 && (R.K & (R.K - 1)) == 0;
+    return np2;
+}
+
+// One edge of at least 4 and rows that fit a block, no replica under load, and few enough trials that launches and
+// waits, not the trials themselves, take the time (kPairBelow).
+bool pairs_colours(const hmc_ctx_s* c)
+{
+    const int64_t Kh = c->reps[0].Kh;
+    bool pairs = c->p.neighbors == 26 && Kh >= 2 && Kh <= 256 && !(c->elastic_buffers && c->any_elastic()) &&
+                 c->n_rep * Kh * Kh * Kh < kPairBelow;
+    for (const RepDev& R : c->reps) pairs = pairs && R.Kh == Kh;
+    return pairs;
+}
+
+hipError_t launch_potts_pair(hmc_ctx_s* c, int pair)
+{
+    PassArgs a = pass_args(c, pair, nullptr);
+    const int Kh = c->reps[0].Kh, rows = 256 / Kh;
+    a.rep_blocks = (Kh * Kh + rows - 1) / rows;
+    const dim3 grid((unsigned)(a.rep_blocks * c->n_rep)), block(256);
+    const int tok = prof_begin(c, kProfPotts);
+    if (pow2_neighbours(c))
+        hipLaunchKernelGGL(k_potts_pair<true>, grid, block, 0, c->stream, a);
+    else
+        hipLaunchKernelGGL(k_potts_pair<false>, grid, block, 0, c->stream, a);
+    prof_end(c, tok);
+    return hipGetLastError();
+}
+
+hipError_t launch_potts_pass(hmc_ctx_s* c, int colour, hmc_trial_record* rec)
+{
+    const PassArgs a = pass_args(c, colour, rec);
     // one site per thread while a pass has fewer chunks than 4 per compute unit and no trial
     // enters the zone-solve list: with the list in use, four times the blocks means four times
     // the same-address list appends (measured at 128^3 under load: 16.2 against 9.6 us)
     const bool one = c->pass_blocks < kPassSplitBelow && !(c->elastic_buffers && c->any_elastic());
     const dim3 grid((unsigned)(one ? 4 * c->pass_blocks : c->pass_blocks)), block(256);
-    bool np2 = true;
-    for (const RepDev& R : c->reps) np2 = np2 && R.proposal == 0 && (R.K & (R.K - 1)) == 0;
+    const bool np2 = pow2_neighbours(c);
     const int tok = prof_begin(c, kProfPotts);
 #define HMC_PASS(MM, SC, SPT)                                                                      \
     do {                                                                                           \
