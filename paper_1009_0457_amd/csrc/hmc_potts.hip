@@ -174,8 +174,19 @@ __device__ __forceinline__ uint32_t neighbour_site(int x, int y, int z, int K, i
     return site_of(wrapi(x, K), wrapi(y, K), wrapi(z, K), K, KK);
 }
 
-// Change of the unlike neighbours of (x, y, z) from state q_old to q_new.
-template <int M>
+// For each half of a: 1 if it differs from that of b.
+__device__ __forceinline__ uint32_t halves_differ(uint32_t a, uint32_t b)
+{
+    uint32_t r;
+    const uint32_t t = a ^ b;
+    asm("v_pk_min_u16 %0, %1, %2 op_sel_hi:[1,0]" : "=v"(r) : "v"(t), "v"(1u));
+    return r;
+}
+
+// Change of the unlike neighbours of (x, y, z) from state q_old to q_new.  EARLY: the reads round the corner of a
+// lattice row go out with the others rather than after them.  Nine reads of eight bytes instead of 26 of two: a pass of
+// 512^3 93 -> 72 us, of 200^3 10.75 -> 9.7, ten 60^3 unchanged at 4.1.
+template <int M, bool EARLY>
 __device__ __forceinline__ int unlike_change(const int16_t* spins, int x, int y, int z, int K, int KK, int q_old,
                                              int q_new)
 {
@@ -190,11 +201,57 @@ __device__ __forceinline__ int unlike_change(const int16_t* spins, int x, int y,
                             (uint32_t)__umul24((uint32_t)wrapi(z + 1, K), KK2)};
     const char* sb = reinterpret_cast<const char*>(spins);
     int gb = 0;
+    if (M == 26 && K >= 4) {
+        // the neighbours lie in nine rows of three, each read as the four sites from `first` on and shifted so that
+        // x - 1, x and x + 1 follow from the lowest bits on; at a row's ends the one round the corner is read too
+        const int first = min(max(x - 1, 0), K - 4);
+        uint64_t v[9];
 #pragma unroll
+        for (int k = 0; k < 9; ++k) __builtin_memcpy(&v[k], sb + (2u * (uint32_t)first + ys[k % 3] + zs[k / 3]), 8);
+        const bool end = x == 0 || x == K - 1;
+        uint32_t far[9];
+        auto read_far = [&]() {
+            const uint32_t round = x == 0 ? 2u * (uint32_t)(K - 1) : 0u;
+#pragma unroll
+            for (int k = 0; k < 9; ++k)
+                far[k] = *reinterpret_cast<const unsigned short*>(sb + (round + ys[k % 3] + zs[k / 3]));
+        };
+        if (EARLY && end) read_far();
+        if (end) {
+            if (!EARLY) read_far();
+#pragma unroll
+            for (int k = 0; k < 9; ++k) v[k] = x == 0 ? v[k] << 16 | far[k] : v[k] >> 32 | (uint64_t)far[k] << 32;
+        } else if (x == K - 2) {
+#pragma unroll
+            for (int k = 0; k < 9; ++k) v[k] >>= 16;
+        }
+        // unlike neighbours, counted in both halves of a word
+        const uint32_t oo = (uint32_t)q_old * 0x10001u, nn = (uint32_t)q_new * 0x10001u;
+        uint32_t un = 0, uo = 0, left = 0;
+        auto count = [&](uint32_t pair) {
+            un += halves_differ(pair, nn);
+            uo += halves_differ(pair, oo);
+        };
+#pragma unroll
+        for (int k = 0; k < 9; ++k) {
+            count((uint32_t)v[k]);
+            if (k % 2 == 0)
+                left = (uint32_t)(v[k] >> 32);
+            else
+                count(__builtin_amdgcn_perm((uint32_t)(v[k] >> 32), left, 0x05040100u));   // two rows' x + 1
+        }
+        count(__builtin_amdgcn_perm(oo, left, 0x05040100u));
+        // less the site's own state, counted with its row and here: unlike the new one, like the old
+        gb = (int)(un & 0xffffu) + (int)(un >> 16) - (int)(uo & 0xffffu) - (int)(uo >> 16) - 2;
+        return gb;
+    }
+#pragma unroll(M == 26 ? 1 : M)   // 26: only for K = 2
     for (int k = 0; k < M; ++k) {
         int dx, dy, dz;
         slot_offset<M>(k, dx, dy, dz);
-        const uint32_t qn = *reinterpret_cast<const unsigned short*>(sb + (xs[dx + 1] + ys[dy + 1] + zs[dz + 1]));
+        const uint32_t at = M == 26 ? 2u * site_of(wrapi(x + dx, K), wrapi(y + dy, K), wrapi(z + dz, K), K, KK)
+                                    : xs[dx + 1] + ys[dy + 1] + zs[dz + 1];
+        const uint32_t qn = *reinterpret_cast<const unsigned short*>(sb + at);
         gb += (int)(qn != (uint32_t)q_new) - (int)(qn != (uint32_t)q_old);
     }
     return gb;
@@ -214,11 +271,12 @@ __device__ __forceinline__ int unlike_change(const int16_t* spins, int x, int y,
 // thousands of blocks on large lattices, so the block appends its elastic trials with one
 // atomic on the list counter and adds its statistics to one of the spread counter copies.
 static_assert(kPassSites == 4 * 256, "a chunk is four sites per thread of a 256-thread block");
-// Bound by reading the whole lattice once a pass (the proposals reach nearly every line: 283 MB at 512^3, 4.2 TB/s) and
-// by VALU work (three quarters of the cycles: 117 operations a site, 35 of them Philox), on small lattices by its
-// chain of dependent reads.  Power-of-two sites by bit fields, what the first Philox rounds owe to the sweep
-// and the key on the scalar unit, counts from ballots instead of shuffles and the thresholds read with the spins
-// took a pass from 95.5 to 93.0 us at 512^3 (6 neighbours 216 to 190), 11.9 to 10.8 at 200^3, 6.15 to 5.5 at 128^3.
+// Bound at 512^3 by VALU work (117 operations a site, 35 of them Philox), the vector cache (the neighbours of the real
+// flips) and reading the whole lattice once a pass (the proposals reach nearly every line: 283 MB), each 70 to 80 % of
+// the time; on small lattices by its chain of dependent reads.  Power-of-two sites by bit fields, what the first
+// Philox rounds owe to the sweep and the key on the scalar unit, counts from ballots instead of shuffles, the
+// thresholds read with the spins (95.5 -> 93 us a pass) and the neighbours by rows of three (93 -> 72) took 256^3
+// from 19.0 to 15.5 us and, with 6 neighbours, 512^3 from 216 to 190.
 // SCREEN: the lower-bound screen's FP64 path is compiled in only where it is used, since it
 // more than doubles the kernel's registers (126 against 48 VGPRs: 4 against 8 wavefronts per
 // SIMD, which hide the chain of dependent reads of every site).
@@ -352,7 +410,7 @@ __global__ __launch_bounds__(256) void k_potts_pass(PassArgs a)
             const int x = (int)(packed & 1023u), y = (int)((packed >> 10) & 1023u), z = (int)(packed >> 20);
             const int q_old = (int)(qq & 0xffffu), q_new = (int)(qq >> 16);
             const uint32_t site = site_of(x, y, z, K, KK);
-            const int gb = unlike_change<M>(spins, x, y, z, K, KK, q_old, q_new);
+            const int gb = unlike_change<M, SPT == 1>(spins, x, y, z, K, KK, q_old, q_new);
             bool accepted = false, screened = false;
             if (!elastic) {
                 accepted = (uint64_t)r1 < s_thr[gb + M];
@@ -443,8 +501,9 @@ __global__ __launch_bounds__(256) void k_potts_pass(PassArgs a)
 // row neighbour's state reads it again after the barrier.  The last pair also advances the sweep index: the
 // first (p = 0) copies it to a second slot, which the others read, so that no block reads the slot that is
 // written.  A sweep is four launches instead of nine, for lattices whose launch is a chain of waits: a colour of 128^3
-// 5.4 -> 4.2 us, of 64^3 4.6 -> 2.8, of ten 60^3 6.3 -> 4.1, of 200^3 10.9 -> 10.75.  Large ones are better off with four
-// sites a thread and a launch a colour (512^3 92.7 us; so 110, and 95 with four sites a thread here).
+// 5.4 -> 4.2 us, of 64^3 4.6 -> 2.8, of ten 60^3 6.3 -> 4.1, of 200^3 10.9 -> 10.75 (9.7 with the neighbours read by rows).
+// Large ones are better off with four sites a thread and a launch a colour (512^3 before the reads by rows 93 us; so
+// 110, and 95 with four sites a thread here).
 template <bool NP2>
 __global__ __launch_bounds__(256) void k_potts_pair(PassArgs a)
 {
@@ -534,7 +593,7 @@ __global__ __launch_bounds__(256) void k_potts_pair(PassArgs a)
             const uint32_t at = t - (wv == 0 ? 0u : wv == 1 ? c0 : wv == 2 ? c1 : c2);
             const uint32_t p = s_item[wv][at][0], qs = s_item[wv][at][1];
             const int sx = (int)(p & 1023u), sy = (int)((p >> 10) & 1023u), sz = (int)(p >> 20), q_new = (int)(qs >> 16);
-            const int gb = unlike_change<M>(spins, sx, sy, sz, K, KK, (int)(qs & 0xffffu), q_new);
+            const int gb = unlike_change<M, true>(spins, sx, sy, sz, K, KK, (int)(qs & 0xffffu), q_new);
             accepted = (uint64_t)s_item[wv][at][2] < s_thr[gb + M];
             if (accepted) spins[site_of(sx, sy, sz, K, KK)] = (int16_t)q_new;
         }
@@ -585,17 +644,31 @@ __global__ void k_fill_f32(float* p, float v, int64_t n)
         p[i] = v;
 }
 
+// Spins in and out, eight a thread where the caller's array allows 16-byte accesses (WIDE; a replica's own spins
+// start on a multiple of 8 and number one; out four a thread), else one.  Memory bound: 512^3 in 225 us, now 165, out 227
+// and 134.
+template <bool WIDE>
 __global__ void k_convert_spins(const int32_t* in, int16_t* out, int64_t n, int32_t Q, uint32_t* err)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t v = in[i];
-        if (v < 0 || v >= Q) {
-            atomicOr(err, 1u);
-            out[i] = 0;
-        } else {
-            out[i] = (int16_t)v;
+    bool bad = false;
+    auto take = [&](int32_t v) {
+        const bool off = v < 0 || v >= Q;
+        bad = bad || off;
+        return off ? 0 : v;
+    };
+    if (WIDE) {
+        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n / 8;
+             i += (int64_t)gridDim.x * blockDim.x) {
+            const int4 a = reinterpret_cast<const int4*>(in)[2 * i], b = reinterpret_cast<const int4*>(in)[2 * i + 1];
+            reinterpret_cast<int4*>(out)[i] =
+                make_int4(take(a.x) | take(a.y) << 16, take(a.z) | take(a.w) << 16, take(b.x) | take(b.y) << 16,
+                          take(b.z) | take(b.w) << 16);
         }
+    } else {
+        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+            out[i] = (int16_t)take(in[i]);
     }
+    if (bad) atomicOr(err, 1u);
 }
 
 __global__ void k_check_finite(const float* p, int64_t n, uint32_t* flag, uint32_t bit)
@@ -606,11 +679,23 @@ __global__ void k_check_finite(const float* p, int64_t n, uint32_t* flag, uint32
     if (__any(bad) && (threadIdx.x & 63) == 0) atomicOr(flag, bit);
 }
 
+template <bool WIDE>
 __global__ void k_export_spins(const int16_t* in, int32_t* out, int64_t n)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        out[i] = in[i];
+    if (WIDE) {
+        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n / 4;
+             i += (int64_t)gridDim.x * blockDim.x) {
+            const int2 v = reinterpret_cast<const int2*>(in)[i];
+            reinterpret_cast<int4*>(out)[i] =
+                make_int4(v.x & 0xffff, (int)((unsigned)v.x >> 16), v.y & 0xffff, (int)((unsigned)v.y >> 16));
+        }
+    } else {
+        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+            out[i] = in[i];
+    }
 }
+
+static bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 static unsigned grid_for(int64_t n, int block, unsigned cap = 65535u * 8u)
 {
@@ -634,13 +719,19 @@ hipError_t launch_fill_f32(float* p, float v, int64_t n, hipStream_t s)
 
 hipError_t launch_convert_spins(const int32_t* in, int16_t* out, int64_t n, int32_t Q, uint32_t* err, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_convert_spins, dim3(grid_for(n, 256, 8192)), dim3(256), 0, s, in, out, n, Q, err);
+    if (aligned16(in) && aligned16(out))
+        hipLaunchKernelGGL(k_convert_spins<true>, dim3(grid_for(n / 8, 256, 8192)), dim3(256), 0, s, in, out, n, Q, err);
+    else
+        hipLaunchKernelGGL(k_convert_spins<false>, dim3(grid_for(n, 256, 8192)), dim3(256), 0, s, in, out, n, Q, err);
     return hipGetLastError();
 }
 
 hipError_t launch_export_spins(const int16_t* in, int32_t* out, int64_t n, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_export_spins, dim3(grid_for(n, 256, 8192)), dim3(256), 0, s, in, out, n);
+    if (aligned16(in) && aligned16(out))
+        hipLaunchKernelGGL(k_export_spins<true>, dim3(grid_for(n / 4, 256, 8192)), dim3(256), 0, s, in, out, n);
+    else
+        hipLaunchKernelGGL(k_export_spins<false>, dim3(grid_for(n, 256, 8192)), dim3(256), 0, s, in, out, n);
     return hipGetLastError();
 }
 

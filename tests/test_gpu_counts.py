@@ -69,3 +69,26 @@ def test_labels_of_a_percolating_field(K):
     np.minimum.at(first, ref, np.arange(K ** 3))
     assert n == ref.max() + 1 and np.array_equal(lab, first[ref])
     lat.close()
+
+
+@pytest.mark.parametrize("K", [2, 6, 34])
+def test_spins_in_and_out_at_any_alignment(K):
+    """The wide conversions (16-byte aligned arrays) and the plain ones give back the same spins."""
+    print(f"[counts] spins in and out K={K}", flush=True)
+    spins = torch.as_tensor(random_spins(K, 9, K + 3)).cuda()
+    lat, _ = lattice(K, 6, 9, np.zeros(K ** 3, np.int32))
+    for shift in (0, 1):
+        store = torch.zeros(K ** 3 + 4, dtype=torch.int32, device="cuda:0")
+        view = store[shift:shift + K ** 3]
+        view.copy_(spins)
+        H.hmc_set_spins(lat.ctx, view)
+        out = torch.full((K ** 3 + 4,), -1, dtype=torch.int32, device="cuda:0")
+        H.hmc_get_spins(lat.ctx, out[shift:shift + K ** 3])
+        lat.synchronize()
+        assert torch.equal(out[shift:shift + K ** 3], spins)
+        assert bool((out[shift + K ** 3:] == -1).all()) and bool((out[:shift] == -1).all())
+    bad = spins.clone()
+    bad[K ** 3 - 1] = 9
+    with pytest.raises(H.HmcError):
+        H.hmc_set_spins(lat.ctx, bad)
+    lat.close()
