@@ -44,15 +44,6 @@ def zone_flops_per_solve(h: int, nr: int) -> float:
     return nr * (200.0 * nv + 12.0 * nn)
 
 
-def zone_flops_minimal(h: int, nr: int) -> float:
-    """The least FP32 work of one zone solve in the separable form the kernels use: per
-    relaxation step and voxel, the strain from the 8 corners (9 gradient entries as
-    separable sums/differences: 24 + 3 shear sums), the 6x6 stress (36 FMA = 72) and the
-    corner forces (transposed sums: 27); per node the heavy-ball update (3 x 4)."""
-    nv, nn = (2 * h + 1) ** 3, (2 * h + 2) ** 3
-    return nr * (126.0 * nv + 12.0 * nn)
-
-
 REFRESH_BYTES_PER_NODE_STEP = 50.0   # read u, w (24 B) + write u, w (24 B) + spin (2 B)
 
 
@@ -72,8 +63,9 @@ def source_hash(*sources):
     return hashlib.sha256(data).hexdigest()[:16]
 
 
-# the lane-shift zone solve of the 5^3 zone: its template and the unit that instantiates it
-ZONE_H2_SOURCES = ("hmc_zone_h2.hip", "hmc_zone_kernels.h")
+# the zone solve of the 5^3 zone over 200 steps, the explicit step: their units and the device code they share
+ZONE_H2_SOURCES = ("hmc_zone_krylov.hip", "hmc_device.h")
+STEP_SOURCES = ("hmc_elastic.hip", "hmc_device.h")
 
 
 def measured_traffic(key_bytes, key_hash, sources, summary="counters_large128.md"):
@@ -527,7 +519,7 @@ def measure_potts(cfg, K, micro, proposal, steps, warmup):
     colours = 8 if p.neighbors == 26 else 2
     bytes_pass = (2 * colours + 2) * K ** 3 / colours
     ms = kt["total_ms"] / max(1, kt["launches"])
-    ach = bytes_pass / (ms * 1e-3) / 1e9
+    ach = bytes_pass * colours * steps / (kt["total_ms"] * 1e-3) / 1e9   # small lattices: two colours a launch
     tr = measured_traffic("potts512_pass_traffic_bytes_per_launch", "potts_source_sha256_16", "hmc_potts.hip",
                           "bandwidth512.md") if K == 512 else None
     roof = {"kernel": "colour pass", "bound": "hbm", "achieved": round(ach, 1), "peak": PEAK_HBM_GBS,
@@ -785,16 +777,15 @@ def measure_refresh(cfg, K, micro, n, warm, tile_z=0, mp8=False):
     lat.close()
     ks = kt["refresh_step"]
     ms = ks["total_ms"] / max(1, ks["launches"])
-    # 8 points per cell, per cell and step: corner displacements 12 B (each node once), 8 spins
-    # 16 B, 24 corner forces written 96 B and read back 96 B, u and w read and written 48 B
-    per_site = 268.0 / 8 if mp8 else REFRESH_BYTES_PER_NODE_STEP
+    # 8 points per cell, per cell and step: 8 spins 16 B, u and w of its node read and written 48 B
+    per_site = 64.0 / 8 if mp8 else REFRESH_BYTES_PER_NODE_STEP
     ach = per_site * K ** 3 / (ms * 1e-3) / 1e9
-    tr = measured_traffic("refresh512_step_traffic_bytes_per_launch", "elastic_source_sha256_16", "hmc_elastic.hip",
+    tr = measured_traffic("refresh512_step_traffic_bytes_per_launch", "elastic_source_sha256_16", STEP_SOURCES,
                           "bandwidth512.md") if (K == 512 and not mp8 and tile_z == 0) else None
     roof = {"kernel": "global explicit step", "bound": "hbm", "achieved": round(ach, 1),
             "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": round(ach / PEAK_HBM_GBS, 4),
             "traffic": None if tr is None else round(tr), "avg_launch_ms": round(ms, 4), "launches": ks["launches"],
-            "note": (f"{per_site} B per site-step (cell pass, node pass and E fold)" if mp8 else
+            "note": (f"{per_site} B per site-step (spins, and u and w of a node a cell read and written)" if mp8 else
                      f"50 B per node-step; working set {(13 * 4 + 2) * K ** 3 / 2 ** 30:.2f} GiB")}
     fold = round(kt["refresh_other"]["total_ms"] / max(1, kt["refresh_other"]["launches"]), 4)
     return el, roof, fold
@@ -916,31 +907,37 @@ def main():
     fps = zone_flops_per_solve(p.zone_h, p.zone_steps)
     zsec = zt["total_ms"] * 1e-3
     achieved = fps * solves / zsec / 1e12 if zsec > 0 else 0.0
-    workload_zone = (p.zone_h, p.zone_steps) == (2, 200)   # the zone the counters were taken on
+    # the zone and the kernel the counters were taken on
+    workload_zone = (p.zone_h, p.zone_steps) == (2, 200) and a.zone_variant in (0, 3)
     per_solve = measured_traffic("zone_traffic_bytes_per_solve", "zone_source_sha256_16",
                                  ZONE_H2_SOURCES) if workload_zone else None
     spl = solves / max(1, zt["launches"])
-    roof = {"kernel": "zone solve", "bound": "alu", "achieved": round(achieved, 3), "peak": PEAK_FP32_TFLOPS,
-            "unit": "TFLOP/s", "frac": round(achieved / PEAK_FP32_TFLOPS, 4),
+    xfps = measured_traffic("zone_executed_fp32_flop_per_solve", "zone_source_sha256_16", ZONE_H2_SOURCES,
+                            "zone_instruction_mix_large128.md") if workload_zone else None
+    # Priced at the FP32 operations the kernel executes (its VALU counters), where they are known for this build, or at
+    # the method's n_r heavy-ball steps, where the kernel takes those.  A long relaxation is solved by conjugate gradients
+    # in fewer applications of the zone's stiffness: its method_equivalent_tflops is what n_r plain steps a solve would
+    # have to sustain, not work done.
+    plain_steps = p.zone_h < 2 or a.zone_variant not in (0, 3)
+    price = xfps if xfps is not None else fps if plain_steps else None
+    executed = price * solves / zsec / 1e12 if price and zsec > 0 else None
+    roof = {"kernel": "zone solve", "bound": "alu", "achieved": None if executed is None else round(executed, 3),
+            "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
+            "frac": None if executed is None else round(executed / PEAK_FP32_TFLOPS, 4),
+            "priced": "executed FP32 operations (VALU counters)" if xfps is not None else
+                      "method: n_r heavy-ball steps" if plain_steps else None,
             "traffic": None if per_solve is None else round(per_solve * spl),
             "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE x2.0 + WRITE_SIZE, profiles/counters_large128.md)",
             "avg_launch_ms": round(zt["total_ms"] / max(1, zt["launches"]), 4),
-            "flop_per_solve": fps, "solves_per_launch": round(solves / max(1, zt["launches"]), 1)}
-    # the same launches priced at the least work of the kernels' separable form and at the FP32
-    # operations the kernel executes (its VALU counters, lanes without a voxel included)
-    mfps = zone_flops_minimal(p.zone_h, p.zone_steps)
-    roof["flop_per_solve_minimal"] = mfps
-    roof["frac_minimal"] = round(mfps * solves / zsec / 1e12 / PEAK_FP32_TFLOPS, 4) if zsec > 0 else None
-    xfps = measured_traffic("zone_executed_fp32_flop_per_solve", "zone_source_sha256_16", ZONE_H2_SOURCES,
-                            "zone_instruction_mix_large128.md") if workload_zone else None
-    roof["flop_per_solve_executed"] = xfps
-    roof["frac_executed"] = round(xfps * solves / zsec / 1e12 / PEAK_FP32_TFLOPS, 4) if (xfps and zsec > 0) else None
+            "flop_per_solve": price, "flop_per_solve_method": fps, "method_equivalent_tflops": round(achieved, 3),
+            "ns_per_solve": round(zsec / max(1, solves) * 1e9, 2),
+            "solves_per_launch": round(solves / max(1, zt["launches"]), 1)}
     pk = kt["potts"]
     potts_roof = None
     if pk["launches"]:
         colours = 8 if p.neighbors == 26 else 2
         bytes_pass = (2 * colours + 2) * K ** 3 / colours      # (2C+2) B per site-trial of the class
-        ach = bytes_pass * pk["launches"] / (pk["total_ms"] * 1e-3) / 1e9
+        ach = bytes_pass * colours * a.steps / (pk["total_ms"] * 1e-3) / 1e9   # small zero-load lattices: two a launch
         potts_roof = {"kernel": "colour pass", "bound": "hbm", "achieved": round(ach, 1), "peak": PEAK_HBM_GBS,
                       "unit": "GB/s", "frac": round(ach / PEAK_HBM_GBS, 4),
                       "avg_launch_ms": round(pk["total_ms"] / pk["launches"], 4),
@@ -950,7 +947,7 @@ def main():
     if rs["launches"]:
         bytes_step = REFRESH_BYTES_PER_NODE_STEP * K ** 3
         ach = bytes_step * rs["launches"] / (rs["total_ms"] * 1e-3) / 1e9
-        rt = measured_traffic("refresh_step_traffic_bytes_per_launch", "elastic_source_sha256_16", "hmc_elastic.hip")
+        rt = measured_traffic("refresh_step_traffic_bytes_per_launch", "elastic_source_sha256_16", STEP_SOURCES)
         refresh_roof = {"kernel": "global explicit step", "bound": "hbm", "achieved": round(ach, 1),
                         "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": round(ach / PEAK_HBM_GBS, 4),
                         "traffic": None if (rt is None or K != 128) else round(rt),
@@ -1087,14 +1084,12 @@ def saturation_line(a, p, micro, lat, cfg):
     zt = kt["zone"]
     fps = zone_flops_per_solve(q.zone_h, q.zone_steps)
     ach = fps * st["zone_solves"] / (zt["total_ms"] * 1e-3) / 1e12 if zt["total_ms"] > 0 else 0.0
-    log(f"[bench] uniform proposals: {n * q.K ** 3 / el:.4e} site-trials/s, zone {ach:.1f} TFLOP/s")
+    log(f"[bench] uniform proposals: {n * q.K ** 3 / el:.4e} site-trials/s, zone as {ach:.1f} TFLOP/s of the method")
     return {"value": n * q.K ** 3 / el, "unit": "site-trials/s", "steps": n, "ms_per_step": el / n * 1e3,
             "zone_solve_fraction": st["zone_solves"] / (n * q.K ** 3), "zone_solves_per_s": st["zone_solves"] / el,
-            "zone_roofline": {"achieved": round(ach, 3), "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
-                              "frac": round(ach / PEAK_FP32_TFLOPS, 4),
-                              "frac_minimal": round(ach * zone_flops_minimal(q.zone_h, q.zone_steps) / fps
-                                                    / PEAK_FP32_TFLOPS, 4),
-                              "avg_launch_ms": round(zt["total_ms"] / max(1, zt["launches"]), 4)},
+            "zone": {"method_equivalent_tflops": round(ach, 3),
+                     "ns_per_solve": round(zt["total_ms"] * 1e6 / max(1, st["zone_solves"]), 2),
+                     "avg_launch_ms": round(zt["total_ms"] / max(1, zt["launches"]), 4)},
             "note": "uniform proposals (every trial a real flip, f_z = 1) from the state after the timed sweeps"}
 
 

@@ -18,7 +18,7 @@ TILE_DEPTHS = (1, 2, 4, 8, 16, 32)
 
 # zone_variant -> (kernel, trials per work-group as a multiple of one wavefront's)
 ZONE_SHAPES = {1: ("one wavefront per trial", 1), 2: ("node columns, 256-lane work-group", 1),
-               3: ("lane shifts", 1), 4: ("lane shifts", 2), 5: ("lane shifts", 4)}
+               3: ("lane shifts, or conjugate gradients for long relaxations", 1), 4: ("lane shifts", 2), 5: ("lane shifts", 4)}
 
 
 def zone_variants_for(zone_h: int) -> list[int]:
