@@ -150,6 +150,27 @@ bool step_streams_of(int64_t sites) { return sites * 38 > (int64_t)512 << 20; }
 //   100^3 44 / 36 / 38 / 24.4 / 34     128^3 64 / 53 / 52 / 27.3 / 36     144^3 - / 82 / 80 / 48.4 / 45.6
 //   160^3 - / 100 / 99 / 50.5 / 47.4   192^3 - / 182 / 177 / 113 / 99
 // and 32 at 256^3 and 512^3 (64 is within 1 %).
+//
+// From 400 blocks at depth 8 on the step's time follows rounds of 1024 resident blocks (four a compute unit) times
+// the layers a block marches, its own and the halo's: a last round that is nearly empty costs less than a full one but
+// four tenths of it at least.  The depth of 8, 16 and 32 with the least product is taken (the deeper ones, with taller
+// rows where the edge allows, run 3 % faster a layer).  Measured, at the deepest depth with 1024 blocks, or 800 at 16,
+// and so: five 100^3 99.7 and 79.6 us a step, three 64.7 and 50.9, two 43.4 and 38.4, ten 210 and 204, ten 60^3 42.6
+// and 38.8; one 200^3 157 and 143, 224^3 182 and 173; the same depth or time within 1 % for 96^3 to 192^3 alone, 240^3,
+// 320^3, two and three 128^3, four 96^3, six 80^3.
+double march_cost(int n, const hmc_replica* r, int tz)
+{
+    int64_t b = 0;
+    int depth = 0;
+    for (int i = 0; i < n; ++i) {
+        b += tile_blocks_of(r[i].K, tz, 8);
+        depth = std::max(depth, balanced_depth(tz, r[i].K));
+    }
+    const double rounds = (double)b / 1024.0, full = std::floor(rounds), rest = rounds - full;
+    const double last = rest > 0.0 ? std::min(1.0, 0.38 + 0.75 * rest) : 0.0;
+    return (depth + 1.3) * std::max(full + last, rounds + 0.2) * (tz == 8 ? 1.0 : 0.97);
+}
+
 int tile_depth_of(const hmc_params* p, int n, const hmc_replica* r)
 {
     if (p->refresh_tile_z > 0) return p->refresh_tile_z;
@@ -158,9 +179,12 @@ int tile_depth_of(const hmc_params* p, int n, const hmc_replica* r)
         for (int i = 0; i < n; ++i) b += tile_blocks_of(r[i].K, tz, 8);
         return b;
     };
-    if (blocks(32) >= 1024) return 32;
-    if (blocks(16) >= 800) return 16;
-    if (blocks(8) >= 400) return 8;
+    if (blocks(8) >= 400) {
+        int best = 8;
+        for (int tz = 16; tz <= kTileZMax; tz *= 2)
+            if (march_cost(n, r, tz) <= march_cost(n, r, best)) best = tz;
+        return best;
+    }
     if (blocks(1) <= 256) return 1;
     return blocks(2) > 512 && blocks(4) <= 512 ? 4 : 2;
 }
