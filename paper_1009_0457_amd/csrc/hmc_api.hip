@@ -494,7 +494,12 @@ hmc_status enqueue_sweep(hmc_ctx c, bool with_refresh)
         if (st != HMC_OK) return st;
     }
     if (pairs_colours(c)) {   // the last pair advances the sweep index
-        for (int pair = 0; pair < 4; ++pair) HMC_TRY(c, launch_potts_pair(c, pair), "sweep: two colours");
+        static const char* const kPairName[4] = {"hmc colour passes 0 and 1", "hmc colour passes 2 and 3",
+                                                 "hmc colour passes 4 and 5", "hmc colour passes 6 and 7"};
+        for (int pair = 0; pair < 4; ++pair) {
+            TraceRange pair_range(kPairName[pair]);
+            HMC_TRY(c, launch_potts_pair(c, pair), "sweep: two colours");
+        }
         c->host_site_trials += c->total_sites;
         return HMC_OK;
     }
