@@ -80,7 +80,8 @@ typedef struct {
                                trials) per work-group.  0 and 3 take relaxations long enough for
                                it (h = 2 and 3; nickel: from 149 and 232 steps) by conjugate
                                gradients with the heavy-ball steps carried out in their Krylov
-                               basis: the same energies to rounding.  Other values: HMC_EINVAL. */
+                               basis, where the steps are stable and damped (zone_beta to the
+                               power zone_steps at most 1e-7): the same energies to rounding.  Other values: HMC_EINVAL. */
     int32_t zone_screen;    /* 1: skip the zone solve of a trial whose rejection is already
                                certain: the point-zone energy 1/2 sigma_p.(S_old - S_new) sigma_p
                                is a lower bound of the zone's (its relaxation only adds

@@ -483,10 +483,19 @@ __global__ __launch_bounds__(64, 2) void k_zone_krylov(KrylovArgs ka)
 // steps at h = 2 and 3.6 at h = 3 (measured on polycrystals of seven sets of constants).  They have
 // to fit the kernel's T; and one costs 1.15 heavy-ball steps, a heavy-ball step on T 0.04 of one,
 // so that gradients pay from zone_steps = 1.2 of them on.
+// And T has to resolve what the heavy-ball steps leave: m Krylov steps reproduce polynomials of degree 2m, and
+// the steps' residual, of a higher one, only as far as it is smooth (slow modes not reached yet) or damped away,
+// by beta^(n_r / 2) where the steps oscillate.  In double precision on random polycrystals the energies were off
+// by 0.5 beta^n_r of themselves: by 5e-2 for beta = 0.99 and n_r = 200, by 1.5e-5 for 0.95; at beta^n_r = 1e-7
+// (n_r = 149 .. 1000, alpha from a hundredth of the stability bound up to it) by 3e-7, the stop's share.
+// Steps that are not stable for every mode are not taken on T either.
 template <int H>
 bool pays(const hmc_params& p)
 {
     const double lam = std::max(p.C11 + 2 * p.C12, std::max(p.C11 - p.C12, 2 * p.C44));
+    const bool stable = std::fabs(p.zone_beta) < 1.0 && p.zone_alpha >= 0.0 &&
+                        p.zone_alpha * 4.0 * lam <= 2.0 * (1.0 + p.zone_beta);
+    if (!stable || std::pow(std::fabs(p.zone_beta), p.zone_steps) > 1e-7) return false;
     const double mu = 0.5 * (p.C11 - p.C12) / ((2 * H + 1) * (2 * H + 1));
     const double m = (H == 2 ? 3.6 : 4.0) * std::sqrt(4.0 * lam / mu);
     return m <= KrylovShape<H>::CAP && p.zone_steps >= 1.25 * m;
