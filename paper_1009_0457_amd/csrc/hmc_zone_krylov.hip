@@ -479,10 +479,11 @@ __global__ __launch_bounds__(64, 2) void k_zone_krylov(KrylovArgs ka)
 
 // Whether the relaxation of zone_steps heavy-ball steps is taken by conjugate gradients
 // (k_zone_krylov).  With kappa = 4 lambda / mu, lambda the largest eigenvalue of the stiffness and
-// mu = 1/2 (C11 - C12) / (2h+1)^2 the zone's slowest shear, a trial takes some 2.2 to 3.3 sqrt(kappa)
-// steps at h = 2 and 3.6 at h = 3 (measured on polycrystals of seven sets of constants).  They have
+// mu = min(1/2 (C11 - C12), C44) / (2h+1)^2 the zone's slowest shear, a trial takes up to 3.7 sqrt(kappa)
+// steps at h = 2 and 4.2 at h = 3 (random polycrystals of 25 sets of constants, C44 / mu from 0.1 to 10;
+// 4 to 5.4 of them for crystals of little contrast, sqrt(kappa) < 25, which fill half of T).  They have
 // to fit the kernel's T; and one costs 1.15 heavy-ball steps, a heavy-ball step on T 0.04 of one,
-// so that gradients pay from zone_steps = 1.2 of them on.
+// so that gradients pay from zone_steps = 1.2 of them on, and are taken from 1.25 on.
 // And T has to resolve what the heavy-ball steps leave: m Krylov steps reproduce polynomials of degree 2m, and
 // the steps' residual, of a higher one, only as far as it is smooth (slow modes not reached yet) or damped away,
 // by beta^(n_r / 2) where the steps oscillate.  In double precision on random polycrystals the energies were off
@@ -496,7 +497,7 @@ bool pays(const hmc_params& p)
     const bool stable = std::fabs(p.zone_beta) < 1.0 && p.zone_alpha >= 0.0 &&
                         p.zone_alpha * 4.0 * lam <= 2.0 * (1.0 + p.zone_beta);
     if (!stable || std::pow(std::fabs(p.zone_beta), p.zone_steps) > 1e-7) return false;
-    const double mu = 0.5 * (p.C11 - p.C12) / ((2 * H + 1) * (2 * H + 1));
+    const double mu = std::min(0.5 * (p.C11 - p.C12), p.C44) / ((2 * H + 1) * (2 * H + 1));
     const double m = (H == 2 ? 3.6 : 4.0) * std::sqrt(4.0 * lam / mu);
     return m <= KrylovShape<H>::CAP && p.zone_steps >= 1.25 * m;
 }
