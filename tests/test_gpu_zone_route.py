@@ -25,6 +25,13 @@ def test_lightly_damped_steps(K, h, nr, beta):
     Z.test_zone_energies_match_the_heavy_ball_oracle(K, h, nr, Z.NICKEL, 1.0, 1.0, beta)
 
 
+# constants at the edge of the rule, whose trials fill the kernel's table or nearly do
+@pytest.mark.parametrize("K,h,nr,c", [(12, 2, 1000, (100.0, 61.0, 120.0)), (12, 2, 1000, (250.0, 60.0, 29.5)),
+                                      (12, 3, 600, (100.0, 57.0, 120.0))])
+def test_full_tables(K, h, nr, c):
+    Z.test_zone_energies_match_the_heavy_ball_oracle(K, h, nr, c, 1.0, 1.0, None)
+
+
 def energies(K, h, nr, c, variant):
     m = voronoi_polycrystal(K, 10, 70 + K)
     p = H.hmc_default_params(K, 26, h)
