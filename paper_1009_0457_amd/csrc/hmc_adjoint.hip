@@ -248,6 +248,30 @@ struct AdjStepArgs {
     int order;               // logical block order (hmc_set_block_order)
 };
 
+// G of the entries at `at` in its three planes, for subtract_from_G: only read where that stores.
+template <bool ATOMIC>
+__device__ __forceinline__ void read_G(const double* G, int64_t n3, int64_t at, double Gv[3])
+{
+    if (!ATOMIC)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) Gv[k] = G[k * n3 + at];
+}
+
+// G -= g.  Only this voxel's thread adds to an entry, so the order of the sum is the steps' either way.  ATOMIC: an
+// atomic nobody waits for (a backward step at 16^3 9.1 against 10.1 us, at 64^3 22.1 against 22.8), which the hardware
+// may drop on fine-grained, managed or host memory: there G is read with the other fields and stored.
+template <bool ATOMIC>
+__device__ __forceinline__ void subtract_from_G(double* G, int64_t n3, int64_t at, const double Gv[3], const double g[3])
+{
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        if (ATOMIC)
+            unsafeAtomicAdd(&G[k * n3 + at], -g[k]);
+        else
+            G[k * n3 + at] = Gv[k] - g[k];
+    }
+}
+
 // tau = C eta / C44 and, where `owned`, the turning work, for a wavefront's voxels: of one grain with its rows
 // from scalar loads, of several with each lane gathering its own.
 __device__ __forceinline__ void adjoint_voxel(const CubicTab& T, const float* low, int q, bool owned,
@@ -276,12 +300,12 @@ __device__ __forceinline__ void adjoint_voxel(const CubicTab& T, const float* lo
 // sums of the nodal fields and of the voxel stresses in LDS, previous layer in registers):
 // the nodal field a = alpha (w^ + u^) and the forward displacement u_t give each voxel its
 // adjoint strain eta and forward strain eps; tau = C eta is formed once per tile, and the
-// voxels the block owns also add their torques to G (by an atomic nobody waits for: only this voxel's thread
-// adds to an entry, so the order of the sum is the steps') and tau to the block's sums.  Bound by VALU and
+// voxels the block owns also add their torques to G (subtract_from_G) and tau to the block's sums.  Bound by VALU and
 // LDS work (64^3: 38 % of the issue slots, 84 B of fields a node, from L2), so the torque counts:
 // against three FP64 contractions with tables of 21 derivatives a grain it takes a backward step, forward
 // recompute included, from 27.4 to 23.0 us at 64^3, 52.7 to 50.8 at 80^3 and 78.6 to 57.1 at 96^3.  Two wavefronts a SIMD (185
 // registers) rather than three with spills: 22.8 against 23.9 us.
+template <bool ATOMIC>
 __global__ __launch_bounds__(256, 2) void k_adj_step(AdjStepArgs a)
 {
     constexpr int NX = kTileX + 2, NY = kTileY + 2, VX = kTileX + 1, VY = kTileY + 1;
@@ -429,8 +453,10 @@ __global__ __launch_bounds__(256, 2) void k_adj_step(AdjStepArgs a)
             sp_cur[k] = sp[k];
             asm volatile("" ::"v"(sp_cur[k]));   // take them before the loads below are issued
         }
-        // requested in the order needed: the own nodes' w^ and u^, then the next layer's grains
+        // requested in the order needed: G, the own nodes' w^ and u^, then the next layer's grains
         const int64_t zoff = (int64_t)K * K * z;
+        double Gv[3];   // a thread without an owned voxel reads its place all the same
+        read_G<ATOMIC>(a.G, n3, vox_xy[0] + zoff, Gv);
         float wn_in[3] = {0.f, 0.f, 0.f}, un_in[3] = {0.f, 0.f, 0.f};
         const int64_t n = nx + (int64_t)K * ny + zoff;
         if (own) {
@@ -458,8 +484,7 @@ __global__ __launch_bounds__(256, 2) void k_adj_step(AdjStepArgs a)
             if (owned) {
 #pragma unroll
                 for (int I = 0; I < 6; ++I) acc[I] += (double)tau[I];
-#pragma unroll
-                for (int qa = 0; qa < 3; ++qa) unsafeAtomicAdd(&a.G[(int64_t)qa * n3 + vox_xy[k] + zoff], -gq[qa]);
+                subtract_from_G<ATOMIC>(a.G, n3, vox_xy[0] + zoff, Gv, gq);
             }
         }
         __syncthreads();                         // the voxel pair is complete
@@ -487,6 +512,7 @@ __global__ __launch_bounds__(256, 2) void k_adj_step(AdjStepArgs a)
 // together 10.8 -> 9.7 us at 16^3 and 11.3 -> 10.0 at 32^3 against k_adj_step.  From depth 2 on the
 // halo's projector rows and three fields a layer cost more than the shorter chain saves (64^3: 18.0 us
 // against 14.7), and k_adj_step is taken.
+template <bool ATOMIC>
 __global__ __launch_bounds__(kFlatThreads, 3) void k_adj_flat(AdjStepArgs a)
 {
     constexpr int TZ = 1;
@@ -532,9 +558,10 @@ __global__ __launch_bounds__(kFlatThreads, 3) void k_adj_flat(AdjStepArgs a)
     const int lx = t % kTileX, ly = t / kTileX;
     const bool own = t < kTileX * kTileY && x0 + lx < K && y0 + ly < K;
     const int64_t own_n = own ? x0 + lx + (int64_t)K * (y0 + ly) + (int64_t)KK * z0 : 0;
-    double Et[6];
+    double Et[6], Gv[3];
 #pragma unroll
     for (int I = 0; I < 6; ++I) Et[I] = a.E_t[I];
+    read_G<ATOMIC>(a.G, n3, vox_xy + (int64_t)KK * z0, Gv);
     float wo[TZ][3], uo[TZ][3];
 #pragma unroll
     for (int l = 0; l < TZ; ++l)
@@ -591,9 +618,7 @@ __global__ __launch_bounds__(kFlatThreads, 3) void k_adj_flat(AdjStepArgs a)
                 if (add) {
 #pragma unroll
                     for (int I = 0; I < 6; ++I) acc[I] += (double)tau[l & 1][I];
-#pragma unroll
-                    for (int k = 0; k < 3; ++k)
-                        unsafeAtomicAdd(&a.G[k * n3 + vox_xy + (int64_t)KK * (z0 + l - 1)], -g[k]);
+                    subtract_from_G<ATOMIC>(a.G, n3, vox_xy + (int64_t)KK * z0, Gv, g);
                 }
             }
         }
@@ -910,6 +935,12 @@ hmc_status hmc_elastic_backward(hmc_ctx c, void* ws, size_t bytes, double dU, do
     const int n_seg = (n + k - 1) / k;
     // tiles as deep as the forward step's (72^3, depth 4: 33.1 us a step with the recompute, 36.5 at 2)
     const int adj_depth = R.tile_z;
+    // G's kind of memory, asked anew on each call: floating-point atomics on coarse-grained memory of this device alone
+    hipPointerAttribute_t attr{};
+    const bool plain_memory = hipPointerGetAttributes(&attr, G) == hipSuccess && attr.type == hipMemoryTypeDevice &&
+                              !attr.isManaged && attr.allocationFlags == hipDeviceMallocDefault &&
+                              attr.device == c->device;
+    if (!plain_memory) (void)hipGetLastError();   // a refused query is no failure of the call
     // Segment j's forward states are recomputed from its checkpoint into buffer j & 1.  With
     // the auxiliary stream the recomputation of segment j-1 runs while the context's stream
     // takes segment j's adjoint steps (both are latency-bound at this size); events order
@@ -988,10 +1019,14 @@ hmc_status hmc_elastic_backward(hmc_ctx c, void* ws, size_t bytes, double dU, do
             const int tok = prof_begin(c, kProfRefreshStep);
             // the adjoint step keeps 32 x 8 tiles whatever the forward step's rows
             const dim3 grid(tile_blocks_of(R.K, adj_depth, kTileY));
-            if (adj_depth == 1)
-                hipLaunchKernelGGL(k_adj_flat, grid, dim3(kFlatThreads), 0, c->stream, a);
+            if (adj_depth == 1 && plain_memory)
+                hipLaunchKernelGGL(k_adj_flat<true>, grid, dim3(kFlatThreads), 0, c->stream, a);
+            else if (adj_depth == 1)
+                hipLaunchKernelGGL(k_adj_flat<false>, grid, dim3(kFlatThreads), 0, c->stream, a);
+            else if (plain_memory)
+                hipLaunchKernelGGL(k_adj_step<true>, grid, dim3(256), 0, c->stream, a);
             else
-                hipLaunchKernelGGL(k_adj_step, grid, dim3(256), 0, c->stream, a);
+                hipLaunchKernelGGL(k_adj_step<false>, grid, dim3(256), 0, c->stream, a);
             prof_end(c, tok);
             ATRY(hipGetLastError(), "backward: step");
             cur_b = 1 - cur_b;
