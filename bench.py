@@ -908,7 +908,7 @@ def main():
     zsec = zt["total_ms"] * 1e-3
     achieved = fps * solves / zsec / 1e12 if zsec > 0 else 0.0
     # the zone and the kernel the counters were taken on
-    workload_zone = (p.zone_h, p.zone_steps) == (2, 200) and a.zone_variant in (0, 3)
+    workload_zone = (p.zone_h, p.zone_steps) == (2, 200) and a.zone_variant == 0
     per_solve = measured_traffic("zone_traffic_bytes_per_solve", "zone_source_sha256_16",
                                  ZONE_H2_SOURCES) if workload_zone else None
     spl = solves / max(1, zt["launches"])
@@ -918,7 +918,7 @@ def main():
     # the method's n_r heavy-ball steps, where the kernel takes those.  A long relaxation is solved by conjugate gradients
     # in fewer applications of the zone's stiffness: its method_equivalent_tflops is what n_r plain steps a solve would
     # have to sustain, not work done.
-    plain_steps = p.zone_h < 2 or a.zone_variant not in (0, 3)
+    plain_steps = p.zone_h < 2 or a.zone_variant != 0
     price = xfps if xfps is not None else fps if plain_steps else None
     executed = price * solves / zsec / 1e12 if price and zsec > 0 else None
     roof = {"kernel": "zone solve", "bound": "alu", "achieved": None if executed is None else round(executed, 3),

@@ -71,17 +71,18 @@ typedef struct {
     int32_t refresh_steps;  /* explicit steps of each such warm refresh */
     int32_t cold_steps;     /* explicit steps hmc_stress_refresh uses for cold_start with
                                n_steps < 0 */
-    int32_t zone_variant;   /* zone-solve kernel: 0 automatic (3 for h >= 1; 2 for h = 0),
-                               1 one wavefront per trial, 2 node columns across a
+    int32_t zone_variant;   /* zone-solve kernel: 0 automatic (gradients as below; else 3 for h >= 1,
+                               2 for h = 0), 1 one wavefront per trial, 2 node columns across a
                                256-lane work-group (h <= 2), 3 node columns of whole trials per
                                wavefront, x neighbours exchanged by cross-lane moves
                                (1 <= h <= 3), one wavefront per work-group; 4 and 5 the same
                                kernel with two and four wavefronts (twice and four times the
-                               trials) per work-group.  0 and 3 take relaxations long enough for
+                               trials) per work-group.  0 takes relaxations long enough for
                                it (h = 2 and 3; nickel: from 149 and 232 steps) by conjugate
                                gradients with the heavy-ball steps carried out in their Krylov
                                basis, where the steps are stable and damped (zone_beta to the
-                               power zone_steps at most 1e-7): the same energies to rounding.  Other values: HMC_EINVAL. */
+                               power zone_steps at most 1e-7): the same energies to rounding.
+                               hmc_zone_by_gradients says whether.  Other values: HMC_EINVAL. */
     int32_t zone_screen;    /* 1: skip the zone solve of a trial whose rejection is already
                                certain: the point-zone energy 1/2 sigma_p.(S_old - S_new) sigma_p
                                is a lower bound of the zone's (its relaxation only adds
@@ -151,6 +152,10 @@ hmc_status hmc_default_params(hmc_params* p, int32_t K, int32_t neighbors, int32
  * eigenvalue of the stiffness and the slowest shear wave of the mesh, 1/2 (C11 - C12)
  * (2 sin(pi/n))^2 with n = K or K/2 mesh cells per edge.  HMC_EINVAL for other counts. */
 hmc_status hmc_set_material_points(hmc_params* p, int32_t n);
+
+/* 1 if the zone solves of these parameters go by conjugate gradients (zone_variant 0, a relaxation
+ * for which they pay), 0 if by heavy-ball steps or if the parameters are invalid. */
+int32_t hmc_zone_by_gradients(const hmc_params* p);
 
 /* Bytes of device workspace hmc_create needs for these parameters and Q grains
  * (0 if the parameters are invalid). */

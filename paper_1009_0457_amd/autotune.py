@@ -13,12 +13,14 @@ per explicit step, so they do not depend on how many trials happened to be real 
 """
 from __future__ import annotations
 
+from .hmc import hmc_params, hmc_zone_by_gradients
+
 TILE_DEPTHS = (1, 2, 4, 8, 16, 32)
 
 
 # zone_variant -> (kernel, trials per work-group as a multiple of one wavefront's)
-ZONE_SHAPES = {1: ("one wavefront per trial", 1), 2: ("node columns, 256-lane work-group", 1),
-               3: ("lane shifts, or conjugate gradients for long relaxations", 1), 4: ("lane shifts", 2), 5: ("lane shifts", 4)}
+ZONE_SHAPES = {0: ("conjugate gradients", 1), 1: ("one wavefront per trial", 1), 2: ("node columns, 256-lane work-group", 1),
+               3: ("lane shifts", 1), 4: ("lane shifts", 2), 5: ("lane shifts", 4)}
 
 
 def zone_variants_for(zone_h: int) -> list[int]:
@@ -33,10 +35,18 @@ def zone_variants_for(zone_h: int) -> list[int]:
     return out
 
 
+def _gradients(ctx) -> list[int]:
+    p = hmc_params.from_buffer_copy(ctx.params)
+    p.zone_variant = 0
+    return [0] if hmc_zone_by_gradients(p) else []
+
+
 def tune_zone_variant(ctx, zone_h: int, sweeps: int = 1, candidates=None) -> dict:
     """Time ``sweeps`` sweeps of each candidate kernel on ``ctx`` (a Lattice or Batch that is
-    ready to sweep) and leave the fastest selected.  Returns {"best": v, "ms_per_solve": {...}}."""
-    cands = list(candidates) if candidates is not None else zone_variants_for(zone_h)
+    ready to sweep) and leave the fastest selected.  Returns {"best": v, "ms_per_solve": {...}}.
+    The candidates are the kernels of this zone size, and variant 0 where it stands for one of its own
+    (conjugate gradients, for long relaxations)."""
+    cands = list(candidates) if candidates is not None else zone_variants_for(zone_h) + _gradients(ctx)
     score = {}
     for v in cands:
         ctx.set_zone_variant(v)

@@ -1324,6 +1324,11 @@ hmc_status hmc_set_zone_screen(hmc_ctx c, int32_t enable)
     return HMC_OK;
 }
 
+int32_t hmc_zone_by_gradients(const hmc_params* p)
+{
+    return check_common(p) == HMC_OK && p->zone_variant == 0 && krylov_pays(*p) ? 1 : 0;
+}
+
 hmc_status hmc_set_zone_variant(hmc_ctx c, int32_t variant)
 {
     if (!c) return HMC_EINVAL;

@@ -267,6 +267,9 @@ hipError_t launch_check_finite(const float* p, int64_t n, uint32_t* flag, uint32
 bool pairs_colours(const hmc_ctx_s* c);
 hipError_t launch_potts_pair(hmc_ctx_s* c, int pair);
 hipError_t launch_potts_pass(hmc_ctx_s* c, int colour, hmc_trial_record* rec);
+// Whether conjugate gradients (hmc_zone_krylov.hip) serve these parameters' zone solve and are faster than its
+// heavy-ball steps.
+bool krylov_pays(const hmc_params& p);
 hipError_t launch_zone_pass(hmc_ctx_s* c, int colour, hmc_trial_record* rec);
 hipError_t launch_apply_pass(hmc_ctx_s* c, int colour);
 hipError_t launch_reuss(hmc_ctx_s* c);

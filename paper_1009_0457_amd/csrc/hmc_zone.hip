@@ -24,11 +24,11 @@ hipError_t launch_zone_pass(hmc_ctx_s* c, int colour, hmc_trial_record* rec)
     a.alpha = (float)c->p.zone_alpha;
     a.beta = (float)c->p.zone_beta;
     const int h = c->p.zone_h;
-    // automatic: lane shifts for h >= 1 (at h = 3, 1.67e6 solves/s against 3.75e5 for a
-    // wavefront per trial, 128^3 workload, n_r = 400), for long relaxations at h = 2 and 3 with
-    // conjugate gradients; node columns for h = 0
+    // automatic: conjugate gradients for long relaxations at h = 2 and 3; else lane shifts for h >= 1 (at
+    // h = 3, 1.67e6 solves/s against 3.75e5 for a wavefront per trial, 128^3 workload, n_r = 400) and node
+    // columns for h = 0
     const int v = c->p.zone_variant;
-    const bool krylov = (v == 0 || v == 3) && krylov_pays(c->p);
+    const bool krylov = v == 0 && krylov_pays(c->p);
     const bool laneshift = (v == 0 && h >= 1) || v == 3 || v == 4 || v == 5;
     const bool column = !laneshift && ((v == 0 && h <= 2) || v == 2);
     const int tok = prof_begin(c, kProfZone);

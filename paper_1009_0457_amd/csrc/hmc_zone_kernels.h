@@ -897,9 +897,7 @@ __global__ __launch_bounds__(64 * WAVES, H == 1 ? 3 : 2) void k_zone_lane(ZoneAr
 hipError_t launch_zone_lane_h2(int waves, dim3 grid, dim3 block, hipStream_t stream, const ZoneArgs& a);
 hipError_t launch_zone_lane_h3(int waves, dim3 grid, dim3 block, hipStream_t stream, const ZoneArgs& a);
 
-// Whether conjugate gradients (hmc_zone_krylov.hip) serve these parameters' zone solve and are
-// faster than its heavy-ball steps, and the launch over at most max_list trials.
-bool krylov_pays(const hmc_params& p);
+// The conjugate-gradient solve (hmc_zone_krylov.hip) over at most max_list trials.
 void launch_zone_krylov(const hmc_params& p, int64_t max_list, const float* Ptab, hipStream_t stream, ZoneArgs a);
 
 }  // namespace hmc

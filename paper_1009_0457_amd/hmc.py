@@ -101,6 +101,7 @@ _SIGS = [
     ("hmc_get_kernel_times", C.c_int, [C.c_void_p, C.POINTER(hmc_kernel_times)]),
     ("hmc_set_graphs", C.c_int, [C.c_void_p, C.c_int32]),
     ("hmc_set_material_points", C.c_int, [C.POINTER(hmc_params), C.c_int32]),
+    ("hmc_zone_by_gradients", C.c_int32, [C.POINTER(hmc_params)]),
     ("hmc_grain_labels", C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.POINTER(C.c_int64)]),
     ("hmc_default_replica", C.c_int, [C.POINTER(hmc_replica), C.POINTER(hmc_params), C.c_int32, C.c_int32]),
     ("hmc_batch_workspace_bytes", C.c_size_t, [C.POINTER(hmc_params), C.c_int32, C.POINTER(hmc_replica)]),
@@ -299,6 +300,10 @@ def hmc_reset_stats(ctx):
 
 def hmc_set_zone_screen(ctx, enable):
     _check(lib().hmc_set_zone_screen(ctx, int(bool(enable))), ctx)
+
+
+def hmc_zone_by_gradients(p: hmc_params) -> bool:
+    return bool(lib().hmc_zone_by_gradients(C.byref(p)))
 
 
 def hmc_set_zone_variant(ctx, variant):

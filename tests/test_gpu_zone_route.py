@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 
 import test_gpu_zone_krylov as Z
+from paper_1009_0457_amd import autotune as A
 from paper_1009_0457_amd import hmc as H
 from paper_1009_0457_amd.synth import voronoi_polycrystal
 
@@ -64,3 +65,28 @@ def test_route(K, h, nr, c, gradients):
     automatic, steps = energies(K, h, nr, c, 0), energies(K, h, nr, c, 4)
     assert np.count_nonzero(steps) > 20
     assert np.array_equal(automatic, steps) != gradients
+
+
+@pytest.mark.parametrize("K,h,nr", [(10, 2, 200), (8, 3, 400)])
+def test_variant_3_keeps_the_steps(K, h, nr):
+    """One wavefront of whole trials per work-group, at lengths that the automatic choice takes by gradients."""
+    print(f"[zone route] variant 3 K={K} h={h} steps={nr}", flush=True)
+    automatic, one, two = (energies(K, h, nr, Z.NICKEL, v) for v in (0, 3, 4))
+    assert np.array_equal(one, two) and not np.array_equal(one, automatic)
+
+
+def test_autotuner_times_the_gradients():
+    """A long relaxation has variant 0 among the candidates, a short one does not."""
+    for nr, want in ((200, True), (60, False)):
+        m = voronoi_polycrystal(12, 10, 21)
+        p = H.hmc_default_params(12, 26, 2)
+        p.kT, p.proposal, p.zone_steps = 0.8, 1, nr
+        lat = H.Lattice(p, m.Q)
+        lat.set_orientations(m.euler)
+        lat.set_spins(m.spins)
+        lat.set_load([80.0, -60.0, 120.0, 20.0, 0.0, -30.0])
+        lat.stress_refresh(100, True)
+        res = A.tune_zone_variant(lat, 2)
+        print(f"[zone route] autotune steps={nr}: {res}", flush=True)
+        assert ("0" in res["ms_per_solve"]) == want and {"1", "2", "3", "4", "5"} <= set(res["ms_per_solve"])
+        lat.close()
