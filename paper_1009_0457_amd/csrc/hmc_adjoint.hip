@@ -122,8 +122,9 @@ __device__ __forceinline__ void adj_store(double* dst, int I, const double v[5])
 // q1 c1 + q2 c2 of cubic_stress, in units of C44 and FP64, with `l` what the rounding of the rows c left: turned,
 // that rounding moves a torque by 5.4e-8 of its norm over random orientations (three tables of rounded
 // derivatives: 2.5e-8).
+template <class F>
 __device__ __forceinline__ void turning_stress(const float c[kProjUsed], const float l[kProjUsed], float sgn,
-                                               const float e[6], double s[6])
+                                               const F e[6], double s[6])
 {
     double d[kProjUsed];
 #pragma unroll
@@ -141,7 +142,8 @@ __device__ __forceinline__ void turning_stress(const float c[kProjUsed], const f
 
 // m += (the vector of) S H - H S for a stress S and a strain H (engineering shears): the entries
 // (y, z), (z, x) and (x, y).
-__device__ __forceinline__ void add_commutator(const double S[6], const float e[6], double m[3])
+template <class F>
+__device__ __forceinline__ void add_commutator(const double S[6], const F e[6], double m[3])
 {
     const double S0 = S[0], S1 = S[1], S2 = S[2], S3 = S[3], S4 = S[4], S5 = S[5];
     const double H0 = e[0], H1 = e[1], H2 = e[2], H3 = 0.5 * (double)e[3], H4 = 0.5 * (double)e[4],
@@ -152,8 +154,9 @@ __device__ __forceinline__ void add_commutator(const double S[6], const float e[
 }
 
 // g = the changes of eta.C eps / C44 per unit turn of the crystal about x, y and z.
+template <class F>
 __device__ __forceinline__ void turning_work(const float c[kProjUsed], const float l[kProjUsed], float sgn,
-                                             const float eta[6], const float eps[6], double g[3])
+                                             const F eta[6], const F eps[6], double g[3])
 {
     double s[6];
     double m[3] = {0.0, 0.0, 0.0};
@@ -168,6 +171,7 @@ __device__ __forceinline__ void turning_work(const float c[kProjUsed], const flo
 struct AdjInitArgs {
     const int16_t* spins;
     CubicTab C;
+    double lam;              // C.lam in full
     const float* low;        // Q x kProj: what the rounding of C's rows left
     const float* u;
     float* ub;
@@ -179,36 +183,39 @@ struct AdjInitArgs {
     int64_t n3;
 };
 
-// Final-state adjoint, with the stress of the steps (another rounding of the stiffness would leave forces
-// that the final state does not have): u^_n = sum_v B_v^T sigma_v, G_v = 1/2 g(eps, eps) (in units of C44), partial sums
-// of sigma.
+// Final-state adjoint: u^_n = sum_v B_v^T sigma_v, G_v = 1/2 g(eps, eps) (in units of C44), partial sums of sigma.
+// With the steps' rows (another rounding of the stiffness would leave forces that the final state does not have), and
+// strain and stress in double, as the energy is formed: it is that energy's derivative at the state there is, whose
+// error is then of second order in the state's.  The macroscopic strain, rounded, would be off alike in every voxel.
+// Over 14 inputs, with E^ in double at the end too (k_adj_grad), the load derivative's error went from 5.2e-8 to 4.0e-8
+// at 64^3 and from 5.3e-8 to 4.6e-8 at 40^3 (rms); the Euler derivatives' and the energy's stayed.
 __global__ __launch_bounds__(256) void k_adj_init(AdjInitArgs a)
 {
     const int K = a.K;
-    float E[6];
-#pragma unroll
-    for (int I = 0; I < 6; ++I) E[I] = (float)a.state[kE + I];
+    const float zero[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     double acc[6] = {0, 0, 0, 0, 0, 0};
     for (int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; n < a.n3; n += (int64_t)gridDim.x * blockDim.x) {
         const int x = (int)(n % K), y = (int)((n / K) % K), z = (int)(n / ((int64_t)K * K));
-        float f[3] = {0.f, 0.f, 0.f};
+        double f[3] = {0.0, 0.0, 0.0};
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
             const int ca = c & 1, cb = (c >> 1) & 1, cc = c >> 2;
             const int vx = wrapk(x - ca, K), vy = wrapk(y - cb, K), vz = wrapk(z - cc, K);
-            float e[6], s[6];
-            voxel_strain(a.u, a.n3, K, vx, vy, vz, E, e);
+            float row[kProjUsed], d[6];
+            double e[6], s[6];
+            voxel_strain(a.u, a.n3, K, vx, vy, vz, zero, d);
             const int g = a.spins[vx + (int64_t)K * (vy + (int64_t)K * vz)];
-            float row[kProjUsed];
             cubic_row(a.C.P, g, row);
-            cubic_stress(row, a.C, e, s);
-            const float sx = ca ? 0.25f : -0.25f, sy = cb ? 0.25f : -0.25f, sz = cc ? 0.25f : -0.25f;
+#pragma unroll
+            for (int I = 0; I < 6; ++I) e[I] = a.state[kE + I] + (double)d[I];
+            cubic_stress(row, a.lam, 0.0, (double)a.C.sgn, 1.0, e, s);
+            const double sx = ca ? 0.25 : -0.25, sy = cb ? 0.25 : -0.25, sz = cc ? 0.25 : -0.25;
             f[0] += sx * s[0] + sy * s[5] + sz * s[4];
             f[1] += sx * s[5] + sy * s[1] + sz * s[3];
             f[2] += sx * s[4] + sy * s[3] + sz * s[2];
             if (c == 0) {
 #pragma unroll
-                for (int I = 0; I < 6; ++I) acc[I] += a.C.C44 * (double)s[I];
+                for (int I = 0; I < 6; ++I) acc[I] += a.C.C44 * s[I];
                 float low[kProjUsed];
                 double gq[3];
                 cubic_row(a.low, g, low);
@@ -701,13 +708,9 @@ struct AdjGradArgs {
 __global__ __launch_bounds__(256) void k_adj_grad(AdjGradArgs a)
 {
     double Eb[6];
-    float Ebf[6];
     const double inv_n3 = 1.0 / (double)a.n3;
 #pragma unroll
-    for (int I = 0; I < 6; ++I) {
-        Eb[I] = a.adj[kEb + I];
-        Ebf[I] = (float)Eb[I];
-    }
+    for (int I = 0; I < 6; ++I) Eb[I] = a.adj[kEb + I];
     double acc[6] = {0, 0, 0, 0, 0, 0};
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < a.n3; v += (int64_t)gridDim.x * blockDim.x) {
         const int g = a.spins[v];
@@ -732,10 +735,10 @@ __global__ __launch_bounds__(256) void k_adj_grad(AdjGradArgs a)
             const long long fx = llrint(val * kFixScale);
             atomicAdd(&a.grad[(int64_t)g * 3 + q], (unsigned long long)fx);
         }
-        float se[6];
-        symv21(a.Stab + (int64_t)g * kTab, Ebf, se);
+        double se[6];
+        symv21(a.Stab + (int64_t)g * kTab, Eb, se);
 #pragma unroll
-        for (int I = 0; I < 6; ++I) acc[I] += (double)se[I];
+        for (int I = 0; I < 6; ++I) acc[I] += se[I];
     }
     block_sum_to<6>(a.partials, acc);
 }
@@ -924,7 +927,7 @@ hmc_status hmc_elastic_backward(hmc_ctx c, void* ws, size_t bytes, double dU, do
     if (st != HMC_OK) return st;
     c->cur_u = 0;
     {
-        AdjInitArgs a{c->d.spins, cubic_tab(c), low, c->d.u[0], ub[0], wb[0], G, c->d.partials, c->d.state, R.K, n3};
+        AdjInitArgs a{c->d.spins, cubic_tab(c), cubic_lam(c), low, c->d.u[0], ub[0], wb[0], G, c->d.partials, c->d.state, R.K, n3};
         hipLaunchKernelGGL(k_adj_init, dim3(nb), dim3(256), 0, c->stream, a);
         hipLaunchKernelGGL(k_adj_E, dim3(1), dim3(256), 0, c->stream, adj, c->d.partials, nb, R.glob_alphaE);
         ATRY(hipGetLastError(), "backward: start");

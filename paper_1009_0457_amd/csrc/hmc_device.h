@@ -22,8 +22,8 @@ __device__ __forceinline__ int wrap_tile(int a, int K)
 // The same for -K <= a < 2K.
 __device__ __forceinline__ int wrap_once(int a, int K) { return a < 0 ? a + K : (a < K ? a : a - K); }
 
-template <class Tab>
-__device__ __forceinline__ void symv21(Tab c, const float e[6], float s[6])
+template <class Tab, class F>
+__device__ __forceinline__ void symv21(Tab c, const F e[6], F s[6])
 {
     s[0] = c[0] * e[0] + c[1] * e[1] + c[2] * e[2] + c[3] * e[3] + c[4] * e[4] + c[5] * e[5];
     s[1] = c[1] * e[0] + c[6] * e[1] + c[7] * e[2] + c[8] * e[3] + c[9] * e[4] + c[10] * e[5];
@@ -54,10 +54,15 @@ struct CubicTab {
     double C44;           // FP64: a rounded one shifts the macroscopic strain of every solve by up to 6e-8
 };
 
+// CubicTab's lam in double.
+inline double cubic_lam(const hmc_ctx_s* c)
+{
+    return c->p.C12 / c->p.C44 + (c->p.C11 - c->p.C12 - 2.0 * c->p.C44) / c->p.C44 / 3.0;
+}
+
 inline CubicTab cubic_tab(const hmc_ctx_s* c)
 {
-    const double an = (c->p.C11 - c->p.C12 - 2.0 * c->p.C44) / c->p.C44;
-    const double lam = c->p.C12 / c->p.C44 + an / 3.0;
+    const double an = (c->p.C11 - c->p.C12 - 2.0 * c->p.C44) / c->p.C44, lam = cubic_lam(c);
     return {c->d.Ptab, (float)lam, (float)(lam - (double)(float)lam), an < 0 ? -1.f : 1.f, c->p.C44};
 }
 

@@ -725,10 +725,9 @@ hipError_t launch_global_final(hmc_ctx_s* c, bool write_sigma)
 {
     FinalArgs a;
     a.spins = c->d.spins;
-    const double an = (c->p.C11 - c->p.C12 - 2.0 * c->p.C44) / c->p.C44;
     a.P = c->d.Ptab;
-    a.lam = c->p.C12 / c->p.C44 + an / 3.0;
-    a.sgn = an < 0 ? -1.0 : 1.0;
+    a.lam = cubic_lam(c);
+    a.sgn = cubic_tab(c).sgn;
     a.C44 = c->p.C44;
     a.u = c->d.u[c->cur_u];
     a.sigma = write_sigma ? c->d.sigma : nullptr;

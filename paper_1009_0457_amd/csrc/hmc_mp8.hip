@@ -481,7 +481,7 @@ hipError_t launch_mp8_final(hmc_ctx_s* c, bool write_sigma)
     Mp8FinalArgs a;
     a.spins = c->d.spins;
     a.C = cubic_tab(c);
-    a.lam = c->p.C12 / c->p.C44 + (c->p.C11 - c->p.C12 - 2.0 * c->p.C44) / c->p.C44 / 3.0;
+    a.lam = cubic_lam(c);
     a.u = c->d.u[0];
     a.sigma = write_sigma ? c->d.sigma : nullptr;
     a.partials = c->d.partials;
