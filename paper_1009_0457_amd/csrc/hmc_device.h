@@ -67,7 +67,10 @@ inline CubicTab cubic_tab(const hmc_ctx_s* c)
 }
 
 // s = C e / C44 for row c; `on` is 1 (0, with lam and lam_lo 0 too, gives 0 for a row of zeros).  The
-// contractions are spelled out: every kernel and branch that forms a stress gives the same bits.
+// contractions are spelled out: every kernel and branch that forms a stress gives the same bits.  A normal component's
+// largest term comes last, so that the sums before it round less: over random orientations under a uniaxial stress
+// a stress is off by 4.4e-8 (rms, of it 1.6e-8 the row's rounding; 5.7e-8 with that term first, 6.9e-8 with the 21
+// entries of C).
 template <class F>
 __device__ __forceinline__ void cubic_stress(const float c[kProjUsed], F lam, F lam_lo, F sgn, F on, const F e[6],
                                              F s[6])
@@ -84,8 +87,8 @@ __device__ __forceinline__ void cubic_stress(const float c[kProjUsed], F lam, F 
     const F q1 = fma((F)2, p1, p2), q2 = fma((F)2, p2, p1);   // less the third axis' part, -(p1 + p2)
 #pragma unroll
     for (int I = 0; I < 6; ++I) {
-        const F b = I < 3 ? fma(on + on, e[I], h) : on * e[I];
-        s[I] = fma(q2, (F)c[6 + I], fma(q1, (F)c[I], b));
+        const F t = fma(q2, (F)c[6 + I], fma(q1, (F)c[I], I < 3 ? h : on * e[I]));
+        s[I] = I < 3 ? fma(on + on, e[I], t) : t;
     }
 }
 
