@@ -40,8 +40,8 @@ __host__ __device__ inline int mp8_blocks(int K)
 // The cells around a step's tile of nodes: one thread a cell column.
 constexpr int kMp8Threads = 256;
 // From this many blocks a launch (as many as run at once) the points' rows are a load on the vector cache
-// rather than a wait: there a lane whose next point lies in the same grain keeps its row (320^3: 142 -> 117 us a
-// step; 200^3 49.4 -> 48.6; but 64^3, whose waits it adds to, 8.6 -> 9.6).
+// rather than a wait: there a lane whose next point lies in the same grain keeps its row (320^3: 133 -> 117 us a
+// step; 224^3 57 -> 46; 200^3 49.4 -> 48.7; but 64^3, whose waits it adds to, 8.7 -> 9.4, and 96^3 13.8 -> 15.1).
 constexpr int kMp8KeepBlocks = 700;
 
 struct Mp8StepArgs {
@@ -91,8 +91,8 @@ __device__ __forceinline__ void plane_sums(const float t[2][2][3], int j, float&
 // Bound by VALU and, in polycrystals, the gather of the rows: about 950 operations a cell (8 x 35 of them the
 // stresses, 96 the FP64 sums) keep the units busy 60 % of the time at 200^3, the vector cache as long.  A cell
 // pass that wrote 24 corner forces a cell, a node pass that gathered them and a launch for the stress sums, as
-// three launches, took 13.6 us at 16^3, 30.6 at 128^3, 89 at 200^3 and 362 at 320^3; this one 8.0, 19.3, 50 and
-// 117.
+// three launches, took 13.6 us at 16^3, 30.6 at 128^3, 89 at 200^3 and 362 at 320^3; this one 7.9, 19.4, 48.7
+// and 115.
 template <bool KEEP>
 __global__ __launch_bounds__(kMp8Threads, 3) void k_mp8_step(Mp8StepArgs a)
 {
@@ -409,11 +409,13 @@ int step_blocks(int K)
 }  // namespace
 
 // In x, y the fewest tiles whose cells, one more than nodes each way, have a thread each, equally wide.  In z
-// the depth whose layers, one more than nodes, cost least: with one, two and three blocks on every CU a
-// layer took 2.4, 3.9 and 5.6 us (three is what its registers allow), and beyond, where blocks follow each other,
-// 1.9 us for each block a CU has and half a block's time at the end.  Measured best depths, and the step there and
-// at half and twice the depth (us): 64^3 1 (8.5, twice 10.9), 128^3 3 (19.4; 21, 22.6), 160^3 5 (26.3;
-// 31.6, 33.0), 200^3 7 (48.6; 59.6, 66.9), 320^3 10 (117; 124, 124).
+// the depth whose layers, one more than nodes, cost least: beside 3.5 us a step, a layer took 2.6, 4.05 and 5.6 us with
+// one, two and three blocks on every CU (three is what its registers allow; 5.3, less for coarse grains, where lanes
+// keep their rows), and beyond, where blocks follow each other, 1.65 us for each block a CU has and 1.7.  The depths it
+// picks, and the step there and at others (us, grains of 8 to 17 sites): 64^3 1 (8.5; 10.8 at 2), 96^3 3 (13.8; 16.3
+// at 4), 128^3 3 (19.4; 20.9 at 2, 26.9 at 5), 160^3 5 (26.3; 31.0 at 2, 30.1 at 4), 176^3 7 (35.8; 43.5 at 4, 46.3 at
+// 10), 200^3 7 (48.7; 52.9 at 4, 50.0 at 10), 224^3 9 (46; 54 at 4, 57 at 13), 256^3 15 (68; 69 at 7, 90 at 14), 280^3
+// 18 (83; 91 at 7, 94 at 14), 300^3 6 (99; 94 at 10, 118 at 30), 320^3 27 (115; 121 at 10, 125 at 18).
 void mp8_tile(int K, int32_t tile[3])
 {
     const int Kc = K / 2;
@@ -428,9 +430,11 @@ void mp8_tile(int K, int32_t tile[3])
     const int tiles = (Kc + tile[0] - 1) / tile[0] * ((Kc + tile[1] - 1) / tile[1]);
     double best = 0.0;
     for (int tz = 1; tz <= std::min(Kc, 32); ++tz) {
-        const double per_cu = tiles * ((Kc + tz - 1) / tz) / 256.0;
-        const double layer = per_cu <= 1 ? 2.4 : per_cu <= 2 ? 3.9 : per_cu <= 3 ? 5.6 : 1.9 * per_cu + 1.9;
-        if (tz == 1 || (tz + 1) * layer < best) best = (tz + 1) * layer, tile[2] = tz;
+        const int blocks = tiles * ((Kc + tz - 1) / tz);
+        const double per_cu = blocks / 256.0, three = blocks > kMp8KeepBlocks ? 5.3 : 5.6;
+        const double layer = per_cu <= 1 ? 2.6 : per_cu <= 2 ? 4.05 : per_cu <= 3 ? three : 1.65 * per_cu + 1.7;
+        const double cost = 3.5 + (tz + 1) * layer;
+        if (tz == 1 || cost < best) best = cost, tile[2] = tz;
     }
 }
 
