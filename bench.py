@@ -64,7 +64,7 @@ def source_hash(*sources):
 
 
 # the zone solve of the 5^3 zone over 200 steps, the explicit step: their units and the device code they share
-ZONE_H2_SOURCES = ("hmc_zone_krylov.hip", "hmc_device.h")
+ZONE_H2_SOURCES = ("hmc_zone_krylov.hip", "hmc_zone_kernels.h", "hmc_device.h")
 STEP_SOURCES = ("hmc_elastic.hip", "hmc_device.h")
 
 
