@@ -85,6 +85,16 @@ def measured_traffic(key_bytes, key_hash, sources, summary="counters_large128.md
         return None
 
 
+def zone_price(gradients, executed, method):
+    """(FP32 operations a zone solve is priced at, what they are): the ones the kernel executes (its VALU counters),
+    where they are known for this build, else the method's n_r heavy-ball steps, where the kernel takes those.  A
+    relaxation that goes by conjugate gradients takes fewer applications of the zone's stiffness: what n_r plain steps
+    would have to sustain is then no work done, and the solve has no price."""
+    if executed is not None:
+        return executed, "executed FP32 operations (VALU counters)"
+    return (None, None) if gradients else (method, "method: n_r heavy-ball steps")
+
+
 def parse():
     ap = argparse.ArgumentParser(description=__doc__.split("\n")[0])
     ap.add_argument("--gpus", type=int, default=1)
@@ -908,24 +918,19 @@ def main():
     zsec = zt["total_ms"] * 1e-3
     achieved = fps * solves / zsec / 1e12 if zsec > 0 else 0.0
     # the zone and the kernel the counters were taken on
-    workload_zone = (p.zone_h, p.zone_steps) == (2, 200) and a.zone_variant == 0
+    gradients = H.hmc_zone_by_gradients(p)
+    workload_zone = (p.zone_h, p.zone_steps) == (2, 200) and gradients
     per_solve = measured_traffic("zone_traffic_bytes_per_solve", "zone_source_sha256_16",
                                  ZONE_H2_SOURCES) if workload_zone else None
     spl = solves / max(1, zt["launches"])
     xfps = measured_traffic("zone_executed_fp32_flop_per_solve", "zone_source_sha256_16", ZONE_H2_SOURCES,
                             "zone_instruction_mix_large128.md") if workload_zone else None
-    # Priced at the FP32 operations the kernel executes (its VALU counters), where they are known for this build, or at
-    # the method's n_r heavy-ball steps, where the kernel takes those.  A long relaxation is solved by conjugate gradients
-    # in fewer applications of the zone's stiffness: its method_equivalent_tflops is what n_r plain steps a solve would
-    # have to sustain, not work done.
-    plain_steps = p.zone_h < 2 or a.zone_variant != 0
-    price = xfps if xfps is not None else fps if plain_steps else None
+    price, priced = zone_price(gradients, xfps, fps)
     executed = price * solves / zsec / 1e12 if price and zsec > 0 else None
     roof = {"kernel": "zone solve", "bound": "alu", "achieved": None if executed is None else round(executed, 3),
             "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
             "frac": None if executed is None else round(executed / PEAK_FP32_TFLOPS, 4),
-            "priced": "executed FP32 operations (VALU counters)" if xfps is not None else
-                      "method: n_r heavy-ball steps" if plain_steps else None,
+            "priced": priced,
             "traffic": None if per_solve is None else round(per_solve * spl),
             "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE x2.0 + WRITE_SIZE, profiles/counters_large128.md)",
             "avg_launch_ms": round(zt["total_ms"] / max(1, zt["launches"]), 4),
