@@ -110,6 +110,24 @@ int balanced_depth(int t, int K)
     return (K + n - 1) / n;
 }
 
+// Whether the shallow kernel (k_global_step_flat) takes the explicit step at depth tz: tiles of 1, 2 or 4 layers, the
+// same in every replica, whose blocks are all resident at once, two a compute unit.  Then the step is one chain of
+// latencies, which that kernel shortens; with more blocks the marched kernel, which holds fewer registers and LDS, is
+// faster.  Measured, us per step shallow and marched, by blocks: depth 1: 128 5.4 / 7.4, 256 (eight 16^3) 6.0 / 7.4, 576
+// 9.7 / 9.3, 1944 18.9 / 17.8; depth 2: 288 7.9 / 9.9, 512 8.6 / 10.4, 972 17.0 / 13.0, 4096 53.7 / 43.3; depth 4: 256
+// 8.8 / 12.4, 512 (sixteen 32^3) 14.0 / 14.3, 600 19.4 / 15.7, 2048 49.9 / 33.8.
+constexpr int64_t kFlatBlocks = 512;
+bool resident_flat(int n, const hmc_replica* r, int tz)
+{
+    if (tz > kFlatDepth) return false;
+    int64_t blocks = 0;
+    for (int i = 0; i < n; ++i) {
+        if (balanced_depth(tz, r[i].K) != tz) return false;
+        blocks += tile_blocks_of(r[i].K, tz);
+    }
+    return blocks <= kFlatBlocks;
+}
+
 // Node rows per block of the forward explicit step at depth tz: the tallest of 32 (1024-thread
 // blocks, one per compute unit), 16 (512 threads, two) and 8 (256 threads, four) that divides
 // every replica's edge and still launches at least 512 blocks; taller tiles re-read fewer halo
@@ -118,7 +136,7 @@ int balanced_depth(int t, int K)
 // 2: 15.1 us per step on 256 blocks of 16 rows against 14.6 us on 512 of 8).
 int tile_rows_of(int n, const hmc_replica* r, int tz)
 {
-    if (tz <= kFlatDepth) return 8;
+    if (resident_flat(n, r, tz)) return 8;
     for (int ty = 32; ty >= 16; ty /= 2) {
         int64_t blocks = 0;
         bool fits = true;
@@ -143,13 +161,15 @@ bool step_streams_of(int64_t sites) { return sites * 38 > (int64_t)512 << 20; }
 // Node layers per block of the explicit step: the caller's choice, else by the number of 32 x 8 blocks
 // the replicas give at each depth.  Deep tiles (8 and more, marched layer by layer) redo the least halo
 // work but want the chip full; below that the step is a chain of memory latencies, and the shallow
-// kernel (k_global_step_flat) takes the depth at which its blocks are all resident, two per compute unit.
-// Measured single lattices, us per step at depth 1 / 2 / 4 / 8 / 16:
-//   32^3 5.3 / 6.1 / 8.0 / 17 / -      48^3 9.3 / 7.8 / 8.4 / 18 / -     64^3 10.6 / 8.4 / 9.0 / 18 / 29
-//   72^3 19 / 16.1 / 14.8 / 18.7 / 29  80^3 22 / 17.7 / 19.8 / 20.9 / 31  96^3 34 / 26 / 27 / 21.4 / 31
-//   100^3 44 / 36 / 38 / 24.4 / 34     128^3 64 / 53 / 52 / 27.3 / 36     144^3 - / 82 / 80 / 48.4 / 45.6
-//   160^3 - / 100 / 99 / 50.5 / 47.4   192^3 - / 182 / 177 / 113 / 99
-// and 32 at 256^3 and 512^3 (64 is within 1 %).
+// kernel takes the depth at which its blocks are all resident (resident_flat).  Where they are not even at depth 4,
+// tiles of that depth are marched.  Measured single lattices, us per step at depth 1 / 2 / 4 / 8 / 16:
+//   32^3 5.6 / 6.2 / 7.7 / 17.5 / -     48^3 9.3 / 8.0 / 8.1 / 17.9 / -      64^3 10.7 / 8.6 / 8.7 / 17.9 / 30
+//   72^3 17.9 / 12.9 / 14.7 / 18.9 / 29  80^3 22 / 18.5 / 15.4 / 20.9 / 31    88^3 25 / 19.7 / 16.2 / 21.2 / 30
+//   96^3 34 / 22.6 / 18.2 / 21.5 / 31    100^3 42 / 30 / 27.5 / 24.4 / 34     128^3 64 / 43 / 34 / 27.2 / 36
+//   144^3 94 / 64 / 52 / 47.8 / 45.1     160^3 120 / 80 / 61 / 49.7 / 46.7    192^3 208 / 148 / 114 / 111 / 102
+// and 16 or 32 at 256^3 (within 3 %), 32 at 512^3 (64 is within 1 %).  The gradient marches its adjoint step at the
+// same depth, whose best is a little deeper: forward and backward together a step takes 58 us at 72^3 at depth 4 and
+// 63 at 2, 97 at 96^3 at 8 and 102 at 4, which is why depth 4 starts at 72^3 and 8 at 92^3.
 //
 // From 400 blocks at depth 8 on the step's time follows rounds of 1024 resident blocks (four a compute unit) times
 // the layers a block marches, its own and the halo's: a last round that is nearly empty costs less than a full one but
@@ -186,7 +206,7 @@ int tile_depth_of(const hmc_params* p, int n, const hmc_replica* r)
         return best;
     }
     if (blocks(1) <= 256) return 1;
-    return blocks(2) > 512 && blocks(4) <= 512 ? 4 : 2;
+    return blocks(2) > kFlatBlocks ? 4 : 2;
 }
 
 Layout layout_of(const hmc_params* p, int n, const hmc_replica* r)
@@ -594,9 +614,7 @@ hmc_status build_context(const hmc_params* p, int n, const hmc_replica* r, void*
     c->node_blocks = L.node_blocks;
     c->tile_blocks = L.tile_blocks;
     c->step_streams = step_streams_of(L.sites);
-    c->flat_depth = L.tile_y == 8 && L.tile_z <= kFlatDepth && !c->step_streams ? L.tile_z : 0;
-    for (int i = 0; i < n; ++i)
-        if (balanced_depth(L.tile_z, r[i].K) != c->flat_depth) c->flat_depth = 0;
+    c->flat_depth = resident_flat(n, r, L.tile_z) ? L.tile_z : 0;
     c->elastic_buffers = L.elastic;
     char* b = (char*)ws;
     c->d.spins = (int16_t*)(b + L.spins);
