@@ -169,7 +169,9 @@ bool step_streams_of(int64_t sites) { return sites * 38 > (int64_t)512 << 20; }
 //   144^3 94 / 64 / 52 / 47.8 / 45.1     160^3 120 / 80 / 61 / 49.7 / 46.7    192^3 208 / 148 / 114 / 111 / 102
 // and 16 or 32 at 256^3 (within 3 %), 32 at 512^3 (64 is within 1 %).  The gradient marches its adjoint step at the
 // same depth, whose best is a little deeper: forward and backward together a step takes 58 us at 72^3 at depth 4 and
-// 63 at 2, 97 at 96^3 at 8 and 102 at 4, which is why depth 4 starts at 72^3 and 8 at 92^3.
+// 63 at 2, 97 at 96^3 at 8 and 102 at 4, which is why depth 4 starts at 72^3 and 8 at 92^3.  A batch, which has no
+// gradient, keeps depth 2 up to 1024 blocks of it (sixty-four 16^3 12.2 us a step at 2 and 14.1 at 4, sixteen 32^3 12.4
+// and 14.0; 1152 blocks, four 48^3, 18.2 and 15.4).
 //
 // From 400 blocks at depth 8 on the step's time follows rounds of 1024 resident blocks (four a compute unit) times
 // the layers a block marches, its own and the halo's: a last round that is nearly empty costs less than a full one but
@@ -206,7 +208,7 @@ int tile_depth_of(const hmc_params* p, int n, const hmc_replica* r)
         return best;
     }
     if (blocks(1) <= 256) return 1;
-    return blocks(2) > kFlatBlocks ? 4 : 2;
+    return blocks(2) <= (n > 1 ? 2 * kFlatBlocks : kFlatBlocks) ? 2 : 4;
 }
 
 Layout layout_of(const hmc_params* p, int n, const hmc_replica* r)
