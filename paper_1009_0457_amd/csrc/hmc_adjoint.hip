@@ -911,8 +911,9 @@ hmc_status hmc_elastic_backward(hmc_ctx c, void* ws, size_t bytes, double dU, do
             const double n[9] = {0.0, 0.0, 1.0, std::cos(e[0]), std::sin(e[0]), 0.0,
                                  std::sin(e[0]) * std::sin(e[1]), -std::cos(e[0]) * std::sin(e[1]), std::cos(e[1])};
             for (int k = 0; k < 9; ++k) ax[(size_t)g * 9 + k] = c->p.C44 * n[k];
-            double proj[kProjUsed];
-            axis_projectors(e, c->p.C11, c->p.C12, c->p.C44, proj);
+            double A[3][3], proj[kProjUsed];
+            bunge(e, A);
+            axis_projectors(A, c->p.C11, c->p.C12, c->p.C44, proj);
             for (int k = 0; k < kProjUsed; ++k) hl[(size_t)g * kProj + k] = (float)(proj[k] - (double)(float)proj[k]);
         }
         ATRY(hipMemcpyAsync(low, hl.data(), hl.size() * sizeof(float), hipMemcpyHostToDevice, c->stream), "backward");

@@ -269,6 +269,8 @@ Layout layout_of(const hmc_params* p, int n, const hmc_replica* r)
 // ------------------------------------------------------------------------------------
 // per-grain tables (Sec. 5)
 // ------------------------------------------------------------------------------------
+}  // namespace
+namespace hmc {
 // Rotation A = Rz(phi1) Rx(Phi) Rz(phi2), crystal -> lab.
 void bunge(const double e[3], double A[3][3])
 {
@@ -286,15 +288,16 @@ void bunge(const double e[3], double A[3][3])
     A[2][2] = c;
 }
 
+}  // namespace hmc
+namespace {
+
 // Lab tables by the 6x6 transformation route: with Voigt pairs (i,j) for row I and (k,l)
 // for column J, T[I][J] = A_ik A_jk (k == l) or A_ik A_jl + A_il A_jk (k != l).  Stress
 // transforms as sigma' = T sigma, so C' = T C T^T; engineering strain transforms with
 // N = D T D^-1 (D = diag(1,1,1,2,2,2)), so S' = N S N^T with the closed-form cubic S.
-void grain_tables(const double e[3], double C11, double C12, double C44, double Cl[36], double Sl[36])
+void grain_tables(const double A[3][3], double C11, double C12, double C44, double Cl[36], double Sl[36])
 {
     static const int pi[6] = {0, 1, 2, 1, 0, 0}, pj[6] = {0, 1, 2, 2, 2, 1};
-    double A[3][3];
-    bunge(e, A);
     double T[6][6], N[6][6];
     for (int I = 0; I < 6; ++I)
         for (int J = 0; J < 6; ++J) {
@@ -746,34 +749,41 @@ hmc_status build_context(const hmc_params* p, int n, const hmc_replica* r, void*
     return HMC_OK;
 }
 
+// The tables of a replica's grains, each padded to its row: one copy for a single lattice, whose three tables follow each
+// other in the workspace, and one a table in a batch.
 hmc_status upload_tables(hmc_ctx c, int rep, const double* euler)
 {
     const RepDev& R = c->reps[rep];
-    std::vector<float> Ct((size_t)R.Q * kTab, 0.f), St((size_t)R.Q * kTab, 0.f), Pt((size_t)R.Q * kProj, 0.f);
+    const size_t Q = (size_t)R.Q, nC = Q * kTab, nP = c->elastic_buffers ? Q * kProj : 0;
+    float* const to[3] = {c->d.Ctab + R.grain_off * kTab, c->d.Stab + R.grain_off * kTab,
+                          nP ? c->d.Ptab + R.grain_off * kProj : nullptr};
+    const size_t n[3] = {nC, nC, nP};
+    const bool one = c->n_rep == 1;
+    const size_t at[3] = {0, one ? (size_t)(to[1] - to[0]) : nC, one && nP ? (size_t)(to[2] - to[0]) : 2 * nC};
+    std::vector<float> host((nP ? at[2] : at[1]) + n[nP ? 2 : 1], 0.f);
+    float *Ct = host.data(), *St = Ct + at[1], *Pt = nP ? Ct + at[2] : nullptr;
     for (int64_t g = 0; g < R.Q; ++g) {
         for (int k = 0; k < 3; ++k)
             if (!std::isfinite(euler[3 * g + k])) return state_fail(c, HMC_ENUMERIC, "non-finite Euler angle");
-        double Cl[36], Sl[36];
-        grain_tables(euler + 3 * g, c->p.C11, c->p.C12, c->p.C44, Cl, Sl);
+        double A[3][3], Cl[36], Sl[36];
+        bunge(euler + 3 * g, A);
+        grain_tables(A, c->p.C11, c->p.C12, c->p.C44, Cl, Sl);
         for (int i = 0; i < 6; ++i)
             for (int j = i; j < 6; ++j) {
                 Ct[(size_t)g * kTab + sym_index(i, j)] = (float)Cl[6 * i + j];
                 St[(size_t)g * kTab + sym_index(i, j)] = (float)Sl[6 * i + j];
             }
+        if (!nP) continue;
         double proj[kProjUsed];
-        axis_projectors(euler + 3 * g, c->p.C11, c->p.C12, c->p.C44, proj);
+        axis_projectors(A, c->p.C11, c->p.C12, c->p.C44, proj);
         for (int i = 0; i < kProjUsed; ++i) Pt[(size_t)g * kProj + i] = (float)proj[i];
     }
-    if (c->elastic_buffers)
-        HMC_TRY(c, hipMemcpyAsync(c->d.Ptab + R.grain_off * kProj, Pt.data(), Pt.size() * sizeof(float),
-                                  hipMemcpyHostToDevice, c->stream),
-                "orientations");
-    HMC_TRY(c, hipMemcpyAsync(c->d.Ctab + R.grain_off * kTab, Ct.data(), Ct.size() * sizeof(float),
-                              hipMemcpyHostToDevice, c->stream),
-            "orientations");
-    HMC_TRY(c, hipMemcpyAsync(c->d.Stab + R.grain_off * kTab, St.data(), St.size() * sizeof(float),
-                              hipMemcpyHostToDevice, c->stream),
-            "orientations");
+    for (int t = 0; t < (one ? 1 : 3); ++t) {
+        const size_t count = one ? host.size() : n[t];
+        if (count)
+            HMC_TRY(c, hipMemcpyAsync(to[t], host.data() + at[t], count * sizeof(float), hipMemcpyHostToDevice, c->stream),
+                    "orientations");
+    }
     HMC_TRY(c, hipStreamSynchronize(c->stream), "orientations");
     std::memcpy(&c->euler[3 * (size_t)c->rep_euler_off[rep]], euler, sizeof(double) * 3 * (size_t)R.Q);
     return HMC_OK;
@@ -865,12 +875,10 @@ namespace hmc {
 
 // The projectors on the first two crystal axes, less a third of 1 each, times
 // sqrt(|C11 - C12 - 2 C44| / C44) (kProj).
-void axis_projectors(const double e[3], double C11, double C12, double C44, double P[kProjUsed])
+void axis_projectors(const double A[3][3], double C11, double C12, double C44, double P[kProjUsed])
 {
     const double sa = std::sqrt(std::fabs(C11 - C12 - 2.0 * C44) / C44);
     static const int pi[6] = {0, 1, 2, 1, 0, 0}, pj[6] = {0, 1, 2, 2, 2, 1};
-    double A[3][3];
-    bunge(e, A);
     for (int m = 0; m < 2; ++m)
         for (int I = 0; I < 6; ++I) P[6 * m + I] = sa * (A[pi[I]][m] * A[pj[I]][m] - (I < 3 ? 1.0 / 3.0 : 0.0));
 }
@@ -1087,7 +1095,9 @@ hmc_status hmc_grain_tables(const double* euler, int32_t Q, double C11, double C
     for (int64_t g = 0; g < Q; ++g) {
         for (int k = 0; k < 3; ++k)
             if (!std::isfinite(euler[3 * g + k])) return HMC_ENUMERIC;
-        grain_tables(euler + 3 * g, C11, C12, C44, C_out + 36 * g, S_out + 36 * g);
+        double A[3][3];
+        bunge(euler + 3 * g, A);
+        grain_tables(A, C11, C12, C44, C_out + 36 * g, S_out + 36 * g);
     }
     return HMC_OK;
 }

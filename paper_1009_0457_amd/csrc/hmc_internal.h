@@ -25,7 +25,8 @@ constexpr int kTab = 24;
 // cost the 512^3 explicit step 2.5 %: 1.666 against 1.625 ms).
 constexpr int kProj = 16, kProjUsed = 12;
 
-void axis_projectors(const double euler[3], double C11, double C12, double C44, double P[kProjUsed]);
+void bunge(const double euler[3], double A[3][3]);
+void axis_projectors(const double A[3][3], double C11, double C12, double C44, double P[kProjUsed]);
 
 __host__ __device__ constexpr int sym_index(int i, int j)
 {
