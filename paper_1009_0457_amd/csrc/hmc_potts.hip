@@ -245,13 +245,20 @@ __device__ __forceinline__ int unlike_change(const int16_t* spins, int x, int y,
         gb = (int)(un & 0xffffu) + (int)(un >> 16) - (int)(uo & 0xffffu) - (int)(uo >> 16) - 2;
         return gb;
     }
-#pragma unroll(M == 26 ? 1 : M)   // 26: only for K = 2
+    if (M == 26) {   // K = 2: the seven other sites, a site that differs in n coordinates being 2^n of the slots
+#pragma unroll
+        for (int k = 1; k < 8; ++k) {
+            const uint32_t at = 2u * (uint32_t)((x ^ (k & 1)) | (y ^ ((k >> 1) & 1)) << 1 | (z ^ (k >> 2)) << 2);
+            const uint32_t qn = *reinterpret_cast<const unsigned short*>(sb + at);
+            gb += ((int)(qn != (uint32_t)q_new) - (int)(qn != (uint32_t)q_old)) << __builtin_popcount(k);
+        }
+        return gb;
+    }
+#pragma unroll
     for (int k = 0; k < M; ++k) {
         int dx, dy, dz;
         slot_offset<M>(k, dx, dy, dz);
-        const uint32_t at = M == 26 ? 2u * site_of(wrapi(x + dx, K), wrapi(y + dy, K), wrapi(z + dz, K), K, KK)
-                                    : xs[dx + 1] + ys[dy + 1] + zs[dz + 1];
-        const uint32_t qn = *reinterpret_cast<const unsigned short*>(sb + at);
+        const uint32_t qn = *reinterpret_cast<const unsigned short*>(sb + (xs[dx + 1] + ys[dy + 1] + zs[dz + 1]));
         gb += (int)(qn != (uint32_t)q_new) - (int)(qn != (uint32_t)q_old);
     }
     return gb;
