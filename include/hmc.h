@@ -353,9 +353,9 @@ hmc_status hmc_batch_texture_histogram(hmc_ctx ctx, int32_t r, const double axis
 /* Grains of replica r (0 for a single lattice): the face-connected clusters of equal spins on
  * the periodic lattice, whose mean volume K^3 / n is the grain size of Sec. 6's growth law.
  * Writes labels_dev[v] (dev, K_r^3 int32, caller-owned) = the smallest site index of the grain
- * of site v, and *n_grains (host).  Iterates label propagation and pointer jumping on the
- * context's stream until nothing changes, synchronising that stream once per round.  Reads the
- * spins as they are after all work enqueued so far. */
+ * of site v, and *n_grains (host).  Unites neighbouring sites of equal spin on the context's
+ * stream and synchronises it once, for the number.  Reads the spins as they are after all work
+ * enqueued so far. */
 hmc_status hmc_grain_labels(hmc_ctx ctx, int32_t r, int32_t* labels_dev, int64_t* n_grains);
 
 /* ---- Adjoint of the global explicit solve (single-lattice contexts) ------------------
@@ -363,7 +363,8 @@ hmc_status hmc_grain_labels(hmc_ctx ctx, int32_t r, int32_t* labels_dev, int64_t
  * the global relaxation (as hmc_stress_refresh(ctx, n_steps, 1)), as a function of every
  * grain's Euler angles theta and the applied stress Sigma.  hmc_elastic_forward runs it and
  * keeps a checkpoint of the state every ckpt_every steps in the caller's adjoint workspace
- * (dev, hmc_adjoint_workspace_bytes, 256-byte aligned); hmc_elastic_backward recomputes one
+ * (dev, hmc_adjoint_workspace_bytes, 256-byte aligned; any kind of memory the device sees,
+ * ordinary device memory being the fastest); hmc_elastic_backward recomputes one
  * segment at a time from those checkpoints and runs the reverse recurrence, returning
  * dU * dU/dtheta (host, Q x 3, per radian) and dU * dU/dSigma (host, 6, per MPa).  The
  * backward call leaves the context at the forward's final state.  The adjoint workspace must

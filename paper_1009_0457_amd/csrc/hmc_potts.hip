@@ -507,10 +507,11 @@ __global__ __launch_bounds__(256) void k_potts_pass(PassArgs a)
 // same spins as two launches.  The draws and reads of both go out first; a second-colour site that proposes its
 // row neighbour's state reads it again after the barrier.  The last pair also advances the sweep index: the
 // first (p = 0) copies it to a second slot, which the others read, so that no block reads the slot that is
-// written.  A sweep is four launches instead of nine, for lattices whose launch is a chain of waits: a colour of 128^3
-// 5.4 -> 4.2 us, of 64^3 4.6 -> 2.8, of ten 60^3 6.3 -> 4.1, of 200^3 10.9 -> 10.75 (9.7 with the neighbours read by rows).
-// Large ones are better off with four sites a thread and a launch a colour (512^3 before the reads by rows 93 us; so
-// 110, and 95 with four sites a thread here).
+// written.  A sweep is four launches instead of nine, for lattices whose launch is a chain of waits: measured, us a
+// colour by single launches and by pairs, both with the neighbours read by rows: 64^3 4.5 and 3.1, 128^3 5.4 and 3.9,
+// ten 60^3 6.2 and 4.4, 160^3 7.5 and 5.8, 200^3 10.7 and 9.3; past the line (kPairBelow) the two meet, ten 100^3 11.0 and
+// 10.1, 256^3 13.8 and 13.3, and large ones are better off with four sites a thread and a launch a colour, 320^3 22.7 and
+// 33.3.
 template <bool NP2>
 __global__ __launch_bounds__(256) void k_potts_pair(PassArgs a)
 {

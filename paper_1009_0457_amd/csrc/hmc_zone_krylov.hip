@@ -10,12 +10,14 @@
 //     Phi = Phi(x) + (Phi_T(n_r heavy-ball steps) - min Phi_T),
 // the first term evaluated at the gradients' x as the other kernels do at their last displacement
 // (its error is of second order in x's), the second, what n_r steps leave of the minimum (some 1e-7
-// of the site's stored energy for the default n_r), from T in double.
+// of the site's stored energy for the default n_r), from T: its heavy-ball steps in FP32 over a trial's lanes, the
+// form of their result in double.
 //
 // A trial stops at the first even step where the residual |b - A x| has been below kKrylovTol |b| for
 // two steps.  Measured in double precision for n_r = 20 .. 400 and h = 1, 2, 3 on random polycrystals,
 // Phi is then within 20 kKrylovTol^2 |Phi| of the heavy-ball value, some 2e-8 of the site's stored
-// energy; the FP32 tables leave 6e-8 of it either way.  The stop is each trial's own, so a trial's
+// energy (nickel; up to 1e-6 of max(|dPi|, W_p / 10) for shears five times as stiff one way as the other); the FP32
+// tables leave 6e-8 of it either way.  The stop is each trial's own, so a trial's
 // result does not depend on which trial shares its wavefront.  It also stops where its T is full.  The rule
 // for taking this kernel (pays, below) leaves no trial far from its end there: for constants at the rule's edge
 // trials in random, layered, checkered and uniform surroundings took at most 126 of the 128 steps at h = 2, and
@@ -487,7 +489,10 @@ __global__ __launch_bounds__(64, 2) void k_zone_krylov(KrylovArgs ka)
 // steps at h = 2 and 4.2 at h = 3 (random polycrystals of 25 sets of constants, C44 / mu from 0.1 to 10;
 // 4 to 5.4 of them for crystals of little contrast, sqrt(kappa) < 25, which fill half of T).  They have
 // to fit the kernel's T; and one costs 1.15 heavy-ball steps, a heavy-ball step on T 0.04 of one,
-// so that gradients pay from zone_steps = 1.2 of them on, and are taken from 1.25 on.
+// so that gradients pay from zone_steps = 1.2 of them on, and are taken from 1.25 on.  Measured there, a pass by
+// heavy-ball steps over one by gradients: h = 2, 149 steps 1.01 to 1.02 at 48^3 and 64^3, 0.93 at 16^3 to 32^3, whose
+// launch lasts as long as its longest trial (1.0 from 160 steps on, 1.2 at 200); h = 3, 232 steps 1.24 at 48^3, 1.02 at
+// 32^3, 0.96 below (1.0 from 245 on).
 // And T has to resolve what the heavy-ball steps leave: m Krylov steps reproduce polynomials of degree 2m, and
 // the steps' residual, of a higher one, only as far as it is smooth (slow modes not reached yet) or damped away,
 // by beta^(n_r / 2) where the steps oscillate.  In double precision on random polycrystals the energies were off
