@@ -498,13 +498,18 @@ __global__ __launch_bounds__(64, 2) void k_zone_krylov(KrylovArgs ka)
 // by beta^(n_r / 2) where the steps oscillate.  In double precision on random polycrystals the energies were off
 // by 0.5 beta^n_r of themselves: by 5e-2 for beta = 0.99 and n_r = 200, by 1.5e-5 for 0.95; at beta^n_r = 1e-7
 // (n_r = 149 .. 1000, alpha from a hundredth of the stability bound up to it) by 3e-7, the stop's share.
-// Steps that are not stable for every mode are not taken on T either.
+// Steps that are not stable for every mode are not taken on T either: alpha times the zone's largest eigenvalue at most
+// 2 (1 + beta).  That eigenvalue is below 4 times the stiffest longitudinal modulus (0.87 to 0.90 of it in uniform and
+// random zones of 11 sets of constants), a bound that leaves room for step lengths set for other constants nearby, as
+// where a program changes C alone (4 lambda, half as large again for nickel, would send those back to the steps).
 template <int H>
 bool pays(const hmc_params& p)
 {
     const double lam = std::max(p.C11 + 2 * p.C12, std::max(p.C11 - p.C12, 2 * p.C44));
+    const double longitudinal = std::max(p.C11, std::max((p.C11 + p.C12 + 2 * p.C44) / 2,
+                                                         (p.C11 + 2 * p.C12 + 4 * p.C44) / 3));   // <100>, <110>, <111>
     const bool stable = std::fabs(p.zone_beta) < 1.0 && p.zone_alpha >= 0.0 &&
-                        p.zone_alpha * 4.0 * lam <= 2.0 * (1.0 + p.zone_beta);
+                        p.zone_alpha * 4.0 * longitudinal <= 2.0 * (1.0 + p.zone_beta);
     if (!stable || std::pow(std::fabs(p.zone_beta), p.zone_steps) > 1e-7) return false;
     const double mu = std::min(0.5 * (p.C11 - p.C12), p.C44) / ((2 * H + 1) * (2 * H + 1));
     const double m = (H == 2 ? 3.6 : 4.0) * std::sqrt(4.0 * lam / mu);

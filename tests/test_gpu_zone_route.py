@@ -26,6 +26,12 @@ def test_lightly_damped_steps(K, h, nr, beta):
     Z.test_zone_energies_match_the_heavy_ball_oracle(K, h, nr, Z.NICKEL, 1.0, 1.0, beta)
 
 
+# steps near the longest that the rule takes on T
+@pytest.mark.parametrize("K,h,nr", [(10, 2, 200), (8, 3, 400)])
+def test_long_steps(K, h, nr):
+    Z.test_zone_energies_match_the_heavy_ball_oracle(K, h, nr, Z.NICKEL, 1.0, 1.55, None)
+
+
 # constants at the edge of the rule, whose trials fill the kernel's table or nearly do
 @pytest.mark.parametrize("K,h,nr,c", [(12, 2, 1000, (100.0, 61.0, 120.0)), (12, 2, 1000, (250.0, 60.0, 29.5)),
                                       (12, 3, 600, (100.0, 57.0, 120.0))])

@@ -41,10 +41,21 @@ def test_slowest_shear(c, nr, want):
 @pytest.mark.parametrize("beta,nr,want", [(0.95, 200, False), (0.95, 314, False), (0.95, 315, True), (0.99, 1000, False),
                                           (0.0, 200, False), (1.0, 4000, False), (-0.5, 200, False), (-1.5, 200, False)])
 def test_damping(beta, nr, want):
-    """0.95^314 is above 1e-7, 0.95^315 below; the default alpha is stable for no beta much below the default's."""
+    """0.95^314 is above 1e-7, 0.95^315 below; the default alpha needs a beta of 0.2 at least to be stable."""
     assert by_gradients(2, nr, beta=beta) == want
 
 
 def test_step_length():
     assert by_gradients(2, 200, alpha_scale=0.01) and by_gradients(2, 200, beta=0.0, alpha_scale=0.5)
-    assert not by_gradients(2, 200, alpha_scale=1.01) and not by_gradients(2, 200, alpha_scale=-1.0)
+    # stable up to 2 (1 + beta) over 4 times the <111> modulus, 346.6 GPa: 1.56 times the default
+    assert by_gradients(2, 200, alpha_scale=1.56) and not by_gradients(2, 200, alpha_scale=1.57)
+    assert not by_gradients(2, 200, alpha_scale=-1.0)
+
+
+def test_constants_changed_alone():
+    """The texture experiment's nickel on another set's step lengths."""
+    for h, nr in ((2, 200), (3, 400)):
+        p = H.hmc_default_params(100, 26, h)
+        p.zone_steps = nr
+        p.C11, p.C12, p.C44 = 250.8, 150.0, 123.5
+        assert H.hmc_zone_by_gradients(p)
