@@ -897,17 +897,16 @@ hmc_status hmc_elastic_backward(hmc_ctx c, void* ws, size_t bytes, double dU, do
     // per-grain derivative tables
     {
         std::vector<float> hS((size_t)Q * 3 * kTab, 0.f), hl((size_t)Q * kProj, 0.f);
-        std::vector<double> dCd((size_t)Q * 108), dSd((size_t)Q * 108), ax((size_t)Q * 9);
-        if (hmc_grain_table_derivatives(c->euler.data(), Q, c->p.C11, c->p.C12, c->p.C44, dCd.data(), dSd.data()) !=
-            HMC_OK)
-            return afail(c, HMC_ENUMERIC, "orientation derivatives");
+        std::vector<double> ax((size_t)Q * 9);
         for (int g = 0; g < Q; ++g) {
+            const double* e = &c->euler[3 * (size_t)g];
+            double dSd[3][36];
+            grain_table_derivatives(e, c->p.C11, c->p.C12, c->p.C44, nullptr, dSd);
             for (int q = 0; q < 3; ++q)
                 for (int i = 0; i < 6; ++i)
                     for (int j = i; j < 6; ++j)
-                        hS[((size_t)g * 3 + q) * kTab + sym_index(i, j)] = (float)dSd[(size_t)g * 108 + q * 36 + 6 * i + j];
+                        hS[((size_t)g * 3 + q) * kTab + sym_index(i, j)] = (float)dSd[q][6 * i + j];
             // phi1 turns about z, Phi about the line of nodes Rz(phi1) x, phi2 about the crystal's z
-            const double* e = &c->euler[3 * (size_t)g];
             const double n[9] = {0.0, 0.0, 1.0, std::cos(e[0]), std::sin(e[0]), 0.0,
                                  std::sin(e[0]) * std::sin(e[1]), -std::cos(e[0]) * std::sin(e[1]), std::cos(e[1])};
             for (int k = 0; k < 9; ++k) ax[(size_t)g * 9 + k] = c->p.C44 * n[k];

@@ -333,9 +333,11 @@ void grain_tables(const double A[3][3], double C11, double C12, double C44, doub
 
 // Derivatives of the lab tables with respect to the three Euler angles (phi1, Phi, phi2):
 // dA by differentiating one factor of Rz(phi1) Rx(Phi) Rz(phi2), then the product rule on
-// the quadratic transformation entries and on C' = T C T^T, S' = N S N^T.
-void grain_table_derivatives(const double e[3], double C11, double C12, double C44, double dCl[3][36],
-                             double dSl[3][36])
+// the quadratic transformation entries and on C' = T C T^T, S' = N S N^T.  dCl may be null.
+}  // namespace
+namespace hmc {
+void grain_table_derivatives(const double e[3], double C11, double C12, double C44, double (*dCl)[36],
+                             double (*dSl)[36])
 {
     static const int pi[6] = {0, 1, 2, 1, 0, 0}, pj[6] = {0, 1, 2, 2, 2, 1};
     const double c1 = std::cos(e[0]), s1 = std::sin(e[0]);
@@ -398,14 +400,16 @@ void grain_table_derivatives(const double e[3], double C11, double C12, double C
                 double vc = 0.0, vs = 0.0;
                 for (int a = 0; a < 6; ++a)
                     for (int b = 0; b < 6; ++b) {
-                        vc += dT[I][a] * Cc[a][b] * T[J][b] + T[I][a] * Cc[a][b] * dT[J][b];
+                        if (dCl) vc += dT[I][a] * Cc[a][b] * T[J][b] + T[I][a] * Cc[a][b] * dT[J][b];
                         vs += dN[I][a] * Sc[a][b] * N[J][b] + N[I][a] * Sc[a][b] * dN[J][b];
                     }
-                dCl[q][6 * I + J] = vc;
+                if (dCl) dCl[q][6 * I + J] = vc;
                 dSl[q][6 * I + J] = vs;
             }
     }
 }
+}  // namespace hmc
+namespace {
 
 // ------------------------------------------------------------------------------------
 // error helpers

@@ -26,6 +26,8 @@ constexpr int kTab = 24;
 constexpr int kProj = 16, kProjUsed = 12;
 
 void bunge(const double euler[3], double A[3][3]);
+void grain_table_derivatives(const double euler[3], double C11, double C12, double C44, double (*dC)[36],
+                             double (*dS)[36]);
 void axis_projectors(const double A[3][3], double C11, double C12, double C44, double P[kProjUsed]);
 
 __host__ __device__ constexpr int sym_index(int i, int j)
